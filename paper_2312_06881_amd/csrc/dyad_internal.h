@@ -67,6 +67,13 @@ hipError_t launch_simt_gemm(const GemmPass &p, hipStream_t s);
 size_t simt_dw_workspace(const DwPass &p);
 hipError_t launch_simt_dw(const DwPass &p, hipStream_t s);
 
+// fp32 on the fp32 matrix instructions, blocks of a multiple of 4 that n_dyad
+// divides the widths into (else hipErrorNotSupported, launching nothing).  The
+// weight gradient is the tile kernel of launch_simt_dw's plan: `splits` token
+// ranges of tps into `part` (as there), or the gradients when part is null.
+hipError_t launch_f32_gemm(const GemmPass &p, hipStream_t s);
+hipError_t launch_f32_dw_tiles(const DwPass &p, int64_t splits, int64_t tps, float *part, hipStream_t s);
+
 // General weight gradient on the matrix cores (bf16, any shape), token splits
 // summed in order through the workspace: general_dw_workspace() bytes (0 when
 // one split suffices or the path does not apply).

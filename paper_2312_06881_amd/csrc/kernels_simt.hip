@@ -328,6 +328,7 @@ int64_t simt_dw_splits(const DwPass &p, int64_t tiles, int64_t &tps) {
 
 hipError_t launch_simt_gemm(const GemmPass &p, hipStream_t s) {
     if (p.M == 0) return hipSuccess;
+    if (const hipError_t e = launch_f32_gemm(p, s); e != hipErrorNotSupported) return e;
     const int64_t classes = p.out_t ? p.D * p.D : p.D;
     const int64_t per_class = p.out_t ? (p.bn + p.D - 1) / p.D + 1 : p.bn;
     const int64_t col_tiles = (per_class + kT - 1) / kT;
@@ -361,11 +362,14 @@ hipError_t launch_simt_dw(const DwPass &p, hipStream_t s) {
     }
     const int64_t blocks = splits * 2 * p.D * jt * kt;
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    if (p.dtype == kF32)
-        general_dw_kernel<float><<<(unsigned)blocks, 256, 0, s>>>(p, jt, kt, splits, tps, part);
-    else
-        general_dw_kernel<uint16_t><<<(unsigned)blocks, 256, 0, s>>>(p, jt, kt, splits, tps, part);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_f32_dw_tiles(p, splits, tps, part, s);
+    if (e == hipErrorNotSupported) {
+        if (p.dtype == kF32)
+            general_dw_kernel<float><<<(unsigned)blocks, 256, 0, s>>>(p, jt, kt, splits, tps, part);
+        else
+            general_dw_kernel<uint16_t><<<(unsigned)blocks, 256, 0, s>>>(p, jt, kt, splits, tps, part);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess || !part) return e;
     int64_t grid = (2 * per_comp + p.n_out + 255) / 256;
     if (grid > 4096) grid = 4096;
