@@ -28,7 +28,11 @@ struct GemmArgs {
     // neighbours on its XCD share its input rows; 1 output columns outer, so
     // they share its weights (few token panels, large weights)
     int n_major;
+    int group_m;        // pp kernel: token panels per run of tiles
 };
+
+// One launch of the block-ordered large tiles (gemm_pp.h), FORM a PPForm.
+hipError_t launch_pp(int form, bool w_t, const GemmArgs &a, hipStream_t s);
 
 // Epilogue of a BM x BN tile whose accumulators sit in the MFMA layout (wave w
 // owns rows (w / WGN) * WM + 16 i + 4 (lane / 16) + v and internal columns

@@ -1,0 +1,204 @@
+// Tile choice and instances of the grouped GEMM on block-ordered operands
+// (gemm_pp.h).
+#include "gemm_pp.h"
+
+namespace dyad {
+namespace {
+
+template <bool W_T, int FORM>
+hipError_t launch_form(const GemmArgs &a, hipStream_t s) {
+    const int64_t tm = (a.M + 255) / 256;
+    const int64_t w = FORM == kPPRes && a.bn % a.D == 0 ? a.bn / a.D : a.bn;   // a tile's columns lie in a run of w
+    if (w % 256 == 0 && tm * (a.Nout / 256) >= 192) return launch_pp_tile<256, 256, 2, 4, W_T, FORM>(a, s);
+    if (w % 192 == 0 && tm * (a.Nout / 192) >= 192) return launch_pp_tile<256, 192, 4, 2, W_T, FORM>(a, s);
+    if (w % 128 == 0 && tm * (a.Nout / 128) >= 192) return launch_pp_tile<256, 128, 4, 2, W_T, FORM>(a, s);
+    if (w % 128 == 0) return launch_pp_tile<128, 128, 2, 4, W_T, FORM>(a, s);
+    if (w % 64 == 0) return launch_pp_tile<256, 64, 4, 2, W_T, FORM>(a, s);
+    return hipErrorNotSupported;
+}
+
+template <bool W_T>
+hipError_t launch_w(int form, const GemmArgs &a, hipStream_t s) {
+    switch (form) {
+    case kPPPair: return launch_form<W_T, kPPPair>(a, s);
+    case kPPSlice: return launch_form<W_T, kPPSlice>(a, s);
+    case kPPAdd: return launch_form<W_T, kPPAdd>(a, s);
+    case kPPPadAdd: return launch_form<W_T, kPPPadAdd>(a, s);
+    case kPPPadPair: return launch_form<W_T, kPPPadPair>(a, s);
+    case kPPRes: return launch_form<W_T, kPPRes>(a, s);
+    default: return hipErrorNotSupported;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_pp(int form, bool w_t, const GemmArgs &a, hipStream_t s) {
+    return w_t ? launch_w<true>(form, a, s) : launch_w<false>(form, a, s);
+}
+
+// The inverse of deinterleave_kernel: out[n][t*D + r] = in[n][r*W + t] for
+// rows of D*W values.  4*D threads move 32 columns of every residue: 16-byte
+// loads along a residue, transposed in LDS, 16-byte stores.
+__global__ void __launch_bounds__(256) interleave_kernel(const uint16_t *in, uint16_t *out, int64_t M, int W, int D) {
+    __shared__ uint4 buf[256];
+    const int tid = threadIdx.x, per = 4 * D;
+    const int c = tid / per, pc = tid % per;
+    const int spans = W / 32;
+    const int64_t gc = (int64_t)blockIdx.x * (256 / per) + c;
+    const bool ok = c < 256 / per && gc < M * spans;
+    const int64_t n = ok ? gc / spans : 0, kc = ok ? gc % spans : 0;
+    const int64_t N = (int64_t)W * D;
+    uint16_t *span = reinterpret_cast<uint16_t *>(buf + c * per);
+    if (ok) {
+        const int r = pc / 4, t0 = (pc % 4) * 8;
+        const uint4 v = *reinterpret_cast<const uint4 *>(in + n * N + (int64_t)r * W + kc * 32 + t0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) span[(t0 + e) * D + r] = (uint16_t)(word_of(v, e >> 1) >> (16 * (e & 1)));
+    }
+    __syncthreads();
+    if (ok) *reinterpret_cast<uint4 *>(out + n * N + kc * 32 * D + pc * 8) = buf[c * per + pc];
+}
+
+hipError_t launch_interleave(const uint16_t *in, uint16_t *out, int64_t M, int64_t W, int D, hipStream_t s) {
+    if (D < 1 || D > 64 || W % 32 != 0 || M < 0) return hipErrorNotSupported;
+    if (M == 0) return hipSuccess;
+    const int64_t groups = M * (W / 32), per_block = 256 / (4 * D);
+    const int64_t blocks = (groups + per_block - 1) / per_block;
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorNotSupported;
+    interleave_kernel<<<(unsigned)blocks, 256, 0, s>>>(in, out, M, (int)W, D);
+    return hipGetLastError();
+}
+
+// Residue-major columns in whole tiles: every (block, residue) pair of the
+// output holds a multiple of 128 or 192 columns (64-column tiles lost to the
+// slice: n_dyad 8, 4096 tokens, 16384 -> 4096 input gradient with 64 columns
+// a pair 397 against 299 us).
+static bool res_columns(const GemmPass &p) {
+    return p.out_t && p.bn % p.D == 0 && (p.bn / p.D % 128 == 0 || p.bn / p.D % 192 == 0);
+}
+
+// Whether a pass takes the plain-block form on the large tiles rather than
+// the fused tiles (or, at n_dyad 16, the earlier plain-block tiles).  The form
+// pays for its copies in HBM traffic, so it wants reductions long enough, and
+// blocks wide enough, for the faster multiply to earn that back.  Measured on
+// gfx950 per call against those, M = 2048 to 16384 tokens:
+//   no output transpose: n_dyad 8 from blocks of 256 1.35-2.1x (2048 -> 8192,
+//     8192 tokens: 242 -> 120 us; below, 768 -> 3072 0.9x), n_dyad 16
+//     1.2-1.7x; n_dyad 2 and 4 from blocks of 512 both ways 1.2-1.6x (4096 ->
+//     4096, n_dyad 4: 187 -> 149 us; blocks of 256 0.8x).
+//   output transpose, residue-major: n_dyad 8 and 16 from reduction blocks of
+//     256 1.1-1.5x without a stashed pre-activation or GELU' (whose extra
+//     copies take the gain: 0.85-1.0x); n_dyad 2 and 4 from 512 (with an input
+//     copy as well from 1024) 1.04-1.6x (4096 -> 4096, n_dyad 4: 241 -> 153 us).
+//   output transpose, slice: n_dyad 8 from reduction blocks of 512 and output
+//     blocks of 256 1.4-1.7x (8192 -> 2048: 196 -> 118 us), n_dyad 2 and 4
+//     without an input copy from 1024 1.15-1.25x; n_dyad 16 0.9-1.0x.
+// n_dyad 2 and 4 also want 192 tiles of 256 x 256: with fewer, the fused
+// tiles' smaller ones fill the GPU better (0.94x at 128 tiles).
+bool pp_pays(const GemmPass &p) {
+    if (p.M <= 1024 || p.bk % kStageK != 0 || p.bn % 64 != 0) return false;
+    const bool h = p.h_out != nullptr || p.epilogue == kEpiGeluGrad;
+    const bool res = res_columns(p);
+    if (p.D >= 8) {
+        if (!p.out_t) return p.D >= 16 || p.bk >= 256;
+        if (res) return !h && p.bk >= 256;
+        return p.D == 8 && p.bn >= 256 && p.bk >= 512;
+    }
+    if ((p.M + 255) / 256 * (p.Nout / 256) < 192) return false;
+    if (!p.out_t) return p.bk >= 512 && p.bn >= 512;
+    if (res) return !h && p.bk >= (p.in_t ? 1024 : 512);
+    return !p.in_t && p.bn >= 256 && p.bk >= 1024;
+}
+
+// Large batches with a transpose on plain blocks.  An input transpose first de-interleaves the input (residue
+// g's columns k*D + g become the contiguous block g).  Without an output
+// transpose both components then run in one loop (kPPPair).  With one:
+//   - where every (block, residue) pair of the output has whole tiles of
+//     columns, both components still run in one loop over residue-major
+//     columns (kPPRes), and a copy interleaves the bf16 results (4 bytes an
+//     output; a stashed pre-activation or GELU' input moves the same way);
+//   - else component 2's sums go to an fp32 slice in block order, which
+//     component 1's epilogue adds at the block-order place of each output
+//     column (8 bytes an output and a second pass, but with output blocks that
+//     narrow the outputs are few against the reduction).
+// The tokens run in chunks of whole rounds of tiles over the GPU, kept short
+// enough that what passes between the kernels stays in the 256 MB MALL
+// (Dyad-DT 8192 -> 32768, n_dyad 16, 8192 tokens, forward: 1335 us in one
+// chunk, 1138 in chunks of 160 MB).
+constexpr size_t kPPChunkBytes = (size_t)160 << 20;
+
+hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s) {
+    if (p.bk % kStageK != 0 || p.bn % 64 != 0) return hipErrorNotSupported;
+    const int D = (int)p.D;
+    const bool res = res_columns(p);
+    const bool slices = p.out_t && !res;
+    const bool keep_h = res && p.epilogue == kEpiBiasGelu && p.h_out;
+    const bool grad = res && p.epilogue == kEpiGeluGrad;
+    const size_t per_tok = (p.in_t ? (size_t)p.Kin * 2 : 0) + (slices ? (size_t)p.Nout * sizeof(float) : 0) +
+                           (res ? (size_t)p.Nout * 2 : 0) + (keep_h || grad ? (size_t)p.Nout * 2 : 0);
+    const size_t wcopy = res && p.w_t ? (size_t)(p.D * p.bn * p.bk) * 2 : 0;
+    int64_t mc = p.M;
+    if (per_tok > 0) {
+        // rounds of 256 tiles of 256 x 256
+        const int64_t round = 256 * ((256 * 256 + p.Nout - 1) / p.Nout);
+        const int64_t fit = (int64_t)((kPPChunkBytes) / per_tok) / round * round;
+        mc = fit > round ? fit : round;
+        if (mc > p.M) mc = p.M;
+    }
+    if (per_tok * (size_t)mc + wcopy > ((size_t)2 << 30)) return hipErrorNotSupported;
+    void *ws = nullptr;
+    if (per_tok + wcopy > 0 && split_workspace(s, per_tok * (size_t)mc + wcopy, &ws) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipErrorNotSupported;
+    }
+    float *slice = static_cast<float *>(ws);
+    uint16_t *yp = reinterpret_cast<uint16_t *>(slice + (slices ? mc * p.Nout : 0));
+    uint16_t *hp = yp + (res ? mc * p.Nout : 0);
+    uint16_t *xp = hp + (keep_h || grad ? mc * p.Nout : 0);
+    uint16_t *w1d = xp + (p.in_t ? mc * p.Kin : 0);
+    GemmArgs a{};
+    a.Kin = p.Kin; a.Nout = p.Nout; a.bk = p.bk; a.bn = p.bn; a.D = p.D;
+    a.bias = static_cast<const uint16_t *>(p.bias);
+    a.epilogue = p.epilogue;
+    a.W1 = static_cast<const uint16_t *>(p.W1);
+    a.W2 = static_cast<const uint16_t *>(p.W2);
+    hipError_t e = hipSuccess;
+    if (wcopy) {
+        e = launch_deinterleave(a.W1, w1d, p.D * p.bk, p.bn / p.D, D, s);
+        a.W1 = w1d;
+    }
+    for (int64_t m0 = 0; m0 < p.M && e == hipSuccess; m0 += mc) {
+        a.M = p.M - m0 < mc ? p.M - m0 : mc;
+        a.in = static_cast<const uint16_t *>(p.in) + m0 * p.Kin;
+        a.in2 = a.in;
+        uint16_t *out = static_cast<uint16_t *>(p.out) + m0 * p.Nout;
+        uint16_t *h_out = p.h_out ? static_cast<uint16_t *>(p.h_out) + m0 * p.Nout : nullptr;
+        const uint16_t *h_in = p.h_in ? static_cast<const uint16_t *>(p.h_in) + m0 * p.Nout : nullptr;
+        if (p.in_t) {
+            e = launch_deinterleave(a.in, xp, a.M, p.bk, D, s);
+            a.in2 = xp;
+        }
+        if (res) {
+            if (e == hipSuccess && grad) e = launch_deinterleave(h_in, hp, a.M, p.Nout / D, D, s);
+            a.out = yp; a.h_out = keep_h ? hp : nullptr; a.h_in = grad ? hp : nullptr;
+            if (e == hipSuccess) e = launch_pp(kPPRes, p.w_t, a, s);
+            if (e == hipSuccess) e = launch_interleave(yp, out, a.M, p.Nout / D, D, s);
+            if (e == hipSuccess && keep_h) e = launch_interleave(hp, h_out, a.M, p.Nout / D, D, s);
+        } else if (!p.out_t) {
+            a.out = out; a.h_out = h_out; a.h_in = h_in;
+            if (e == hipSuccess) e = launch_pp(kPPPair, p.w_t, a, s);
+        } else {
+            GemmArgs c2 = a;
+            c2.in = a.in2; c2.W1 = a.W2;
+            c2.bias = nullptr; c2.h_in = nullptr; c2.out = nullptr; c2.h_out = nullptr; c2.epilogue = kEpiBias;
+            c2.part = slice; c2.unperm = 0;
+            if (e == hipSuccess) e = launch_pp(kPPSlice, p.w_t, c2, s);
+            a.out = out; a.h_out = h_out; a.h_in = h_in;
+            a.part = slice; a.unperm = 1;
+            if (e == hipSuccess) e = launch_pp(kPPAdd, p.w_t, a, s);
+        }
+    }
+    return e;
+}
+
+}  // namespace dyad

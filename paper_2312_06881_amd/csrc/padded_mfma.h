@@ -37,6 +37,7 @@ hipError_t launch_pad_tile(const GemmArgs &a0, hipStream_t s) {
 // multiple of 256, 192, 128 or 64 columns, 8-wave tiles where they fill the GPU.
 template <bool W_T, int ONLY>
 hipError_t launch_pad_form(const GemmArgs &a, hipStream_t s) {
+    if (const hipError_t e = launch_pp(ONLY, W_T, a, s); e != hipErrorNotSupported) return e;
     const int64_t bnp = a.bn;
     auto enough = [&](int bm, int bn_tile) { return ((a.M + bm - 1) / bm) * (a.Nout / bn_tile) >= 256; };
     if (bnp % 256 == 0 && enough(256, 256)) return launch_pad_tile<256, 256, 2, 4, W_T, ONLY>(a, s);
