@@ -114,11 +114,16 @@ constexpr int mg_gb() {
 //   strided, one group:  8 columns (j..j+7)*D + g, eight 2-byte loads;
 //   strided, all groups: chunks of NJ columns of every group (NJ*D consecutive
 //                 input columns, 16-byte loads) split into one NJ-column piece
-//                 per group.
-template <int D, int NG, int W, bool SPAN, int T>
+//                 per group.  At n_dyad 4 with both operands strided a chunk
+//                 is one 16-byte load (NJ = 2), so that consecutive lanes load
+//                 consecutive pieces and four of them fill a 64-byte request
+//                 (Dyad-DT 1024 -> 4096, 16384 tokens: 141 -> 100 us); with one
+//                 operand strided the 4-byte LDS writes cost what that saves
+//                 (Dyad-IT there 113 -> 119 us).
+template <int D, int NG, int W, bool SPAN, int T, bool BOTH>
 struct DwSide {
     static constexpr int kKind = !SPAN ? 0 : (NG == 1 ? 1 : 2);
-    static constexpr int kNJ = D >= 8 ? 32 / D : 8;
+    static constexpr int kNJ = D >= 8 ? 32 / D : BOTH && D == 4 ? 2 : 8;
     static constexpr int kVec = kKind == 2 ? kNJ * D / 8 : 1;           // 16-byte loads per item
     static constexpr int kPerRow = kKind == 2 ? W / kNJ : NG * W / 8;   // items per token row
     static constexpr int kItems = kStageK * kPerRow;
@@ -189,8 +194,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, unsigned char *smem, in
     constexpr int T = C::kThreads;
     constexpr bool SPAN_A = C2 && OUT_T && D > 1;    // dZ columns j*D + g
     constexpr bool SPAN_B = C2 && IN_T && D > 1;     // X columns k*D + g
-    using SA = DwSide<D, L::NG, L::JT, SPAN_A, T>;
-    using SB = DwSide<D, L::NG, L::KT, SPAN_B, T>;
+    using SA = DwSide<D, L::NG, L::JT, SPAN_A, T, SPAN_A && SPAN_B>;
+    using SB = DwSide<D, L::NG, L::KT, SPAN_B, T, SPAN_A && SPAN_B>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
     const int j0 = jt * L::JT, k0 = kt * L::KT;

@@ -58,6 +58,11 @@ struct GemmCfg {
     static constexpr int kRC = kRowChunks / kThreads;
     // 16-byte A vectors per row-chunk a BlockTrans stage loads
     static constexpr int kVecPerRC2 = (IN_T || OUT_T) ? D : 1;
+    // spans loaded piece by piece (put_residue): 3-9 % faster on the 8-wave
+    // 256 x 192 tiles (OPT-125m fc2 forward, Dyad-IT 62.4 -> 57.5 us), 3-4 %
+    // slower on the 4-wave ones and on 256 x 256 under an output transpose,
+    // where the narrower LDS writes cost more than the loads save
+    static constexpr bool kPieces = IN_T && (D == 2 || D == 4) && kWaves == 8 && !(OUT_T && BN == 256);
     // B: 16-byte vectors (no transpose) or 8x8 blocks (transpose) per stage
     static constexpr int kVecB = BN * (kStageK / 8);
     static constexpr int kRB = (kVecB + kThreads - 1) / kThreads;
@@ -127,13 +132,21 @@ dyad_gemm_mfma(GemmArgs a) {
     auto internal_col = [](int p) -> int { return OUT_T ? (p % D) * C::kCPR + p / D : p; };
 
     // Per-thread byte offsets, fixed for the whole tile; stages add a scalar offset.
-    uint32_t voA1[C::kRC], voA2[C::kRC];
+    uint32_t voA1[C::kRC], voA2[C::kPieces ? C::kRC * D : C::kRC];
+    if constexpr (C::kPieces) {
+#pragma unroll
+        for (int q = 0; q < C::kRC * D; ++q) {
+            const int v = tid + q * T, row = v / (4 * D), c = v % (4 * D);
+            voA2[q] = (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)c * 16u;
+        }
+    }
 #pragma unroll
     for (int q = 0; q < C::kRC; ++q) {
         const int rc = tid + q * T, row = rc >> 2, c = rc & 3;
         const uint32_t rowoff = (uint32_t)row * (uint32_t)Kin * 2u;
         voA1[q] = rowoff + (uint32_t)(g1 * bk + c * 8) * 2u;
-        if constexpr (IN_T) voA2[q] = rowoff + (uint32_t)(c * 8 * D) * 2u;       // span of 8 k x D residues
+        if constexpr (C::kPieces) continue;
+        else if constexpr (IN_T) voA2[q] = rowoff + (uint32_t)(c * 8 * D) * 2u;       // span of 8 k x D residues
         else if constexpr (OUT_T) voA2[q] = rowoff + (uint32_t)(c * 8) * 2u;     // + block r (scalar)
         else voA2[q] = voA1[q];
     }
@@ -183,6 +196,9 @@ dyad_gemm_mfma(GemmArgs a) {
         for (int q = 0; q < C::kRC; ++q) {
             if constexpr (!C2 || !(IN_T || OUT_T)) {
                 ra[q][0] = bload16(rA, C2 ? voA2[q] : voA1[q], kk * 2u);
+            } else if constexpr (C::kPieces) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) ra[q][d] = bload16(rA, voA2[q * D + d], kk * D * 2u);
             } else if constexpr (IN_T) {
 #pragma unroll
                 for (int d = 0; d < D; ++d) ra[q][d] = bload16(rA, voA2[q] + d * 16u, kk * D * 2u);
@@ -224,6 +240,22 @@ dyad_gemm_mfma(GemmArgs a) {
             const int rc = tid + q * T, row = rc >> 2, c = rc & 3;
             if constexpr (!C2 || !(IN_T || OUT_T)) {
                 *reinterpret_cast<uint4 *>(buf + lds_off(row, c)) = act(ra[q][0]);
+            } else if constexpr (C::kPieces) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const int v = tid + (q * D + d) * T, prow = v / (4 * D), k0 = v % (4 * D) * (8 / D);
+                    uint16_t *dst = buf + lds_off(prow, k0 >> 3) + (k0 & 7);
+                    auto word = [](uint32_t w) -> uint32_t {
+                        if constexpr (GELU_IN) return gelu2(w);
+                        else return w;
+                    };
+                    if constexpr (OUT_T) {
+#pragma unroll
+                        for (int r = 0; r < D; ++r) put_residue<D>(ra[q][d], r, dst + r * C::kSlab, word);
+                    } else {
+                        put_residue<D>(ra[q][d], g1, dst, word);   // only residue g1 feeds this tile
+                    }
+                }
             } else if constexpr (IN_T) {
                 uint4 span[D];
                 if constexpr (OUT_T) {

@@ -51,6 +51,8 @@ struct Gemm2Cfg {
     static constexpr int kUnitsA2 = IN_T ? kRowChunks : kRes * kRowChunks;
     static constexpr int kQA2 = (kUnitsA2 + kThreads - 1) / kThreads;
     static constexpr int kVA2 = IN_T ? D : 1;                           // an input transpose loads spans
+    static constexpr bool kPieces = IN_T && (D == 2 || D == 4) && kRowChunks % kThreads == 0;   // piece by piece (put_residue):
+    // OPT-125m fc1 input gradient, Dyad-OT 68.6 -> 62.2 us
     static constexpr int kUnitsB = W_T ? kStageK * BN / 8 : BN * (kStageK / 8);
     static constexpr int kQB = (kUnitsB + kThreads - 1) / kThreads;
     static constexpr bool kB1Chunks = W_T && OUT_T && D > 1;
@@ -127,13 +129,21 @@ dyad_gemm_mfma2(GemmArgs a) {
         voA1[q] = okA1[q] ? (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)(g1 * bk + c * 8) * 2u : kNoLoad;
         loA1[q] = (uint32_t)lds_off(row, c) * 2u;
     }
-    uint32_t voA2[C::kQA2], loA2[C::kQA2];
+    uint32_t voA2[C::kPieces ? C::kQA2 * D : C::kQA2], loA2[C::kQA2];
+    if constexpr (C::kPieces) {
+#pragma unroll
+        for (int q = 0; q < C::kQA2 * D; ++q) {
+            const int v = tid + q * T, row = v / (4 * D), c = v % (4 * D);
+            voA2[q] = (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)c * 16u;
+        }
+    }
 #pragma unroll
     for (int q = 0; q < C::kQA2; ++q) {
         const int p = (tid + q * T) % C::kUnitsA2;
         okA2[q] = tid + q * T < C::kUnitsA2;
         const int r = IN_T ? 0 : p / C::kRowChunks, rc = p % C::kRowChunks, row = rc >> 2, c = rc & 3;
         const uint32_t rowoff = (uint32_t)row * (uint32_t)Kin * 2u;
+        if constexpr (C::kPieces) continue;
         if constexpr (IN_T) voA2[q] = rowoff + (uint32_t)(c * 8 * D) * 2u;            // span of 8 k x D residues
         else if constexpr (ONLY == 5) voA2[q] = rowoff + (uint32_t)(g1 * bk + c * 8) * 2u;   // block g1 of in2
         else voA2[q] = rowoff + (uint32_t)(r * bk + c * 8) * 2u;                      // residue r's input block
@@ -201,7 +211,10 @@ dyad_gemm_mfma2(GemmArgs a) {
         }
 #pragma unroll
         for (int q = 0; q < (kComp1Only ? 0 : C::kQA2); ++q) {
-            if constexpr (IN_T) {
+            if constexpr (C::kPieces) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) ra2[q][d] = bload16(rA, voA2[q * D + d], kk * D * 2u);
+            } else if constexpr (IN_T) {
 #pragma unroll
                 for (int d = 0; d < D; ++d) ra2[q][d] = bload16(rA, voA2[q] + d * 16u, kk * D * 2u);
             } else {
@@ -225,7 +238,19 @@ dyad_gemm_mfma2(GemmArgs a) {
 #pragma unroll
         for (int q = 0; q < (kComp1Only ? 0 : C::kQA2); ++q) {
             if (C::kUnitsA2 % T != 0 && !okA2[q]) continue;
-            if constexpr (IN_T) {
+            if constexpr (C::kPieces) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const int v = tid + (q * D + d) * T, prow = v / (4 * D), k0 = v % (4 * D) * (8 / D);
+                    uint16_t *dst = reinterpret_cast<uint16_t *>(buf + C::kOffA2) + lds_off(prow, k0 >> 3) + (k0 & 7);
+                    if constexpr (OUT_T) {
+#pragma unroll
+                        for (int r = 0; r < D; ++r) put_residue<D>(ra2[q][d], r, dst + r * (C::kSlab / 2), [](uint32_t w) { return w; });
+                    } else {
+                        put_residue<D>(ra2[q][d], g1, dst, [](uint32_t w) { return w; });   // only residue g1 feeds this tile
+                    }
+                }
+            } else if constexpr (IN_T) {
                 uint4 span[D];
 #pragma unroll
                 for (int d = 0; d < D; ++d) span[d] = ra2[q][d];
