@@ -154,6 +154,9 @@ def _act(a) -> int:
 
 
 def _dtype(*ts) -> int:
+    dt = ts[0].dtype
+    if dt in _DT and all(t is None or t.dtype is dt for t in ts):
+        return _DT[dt]
     dts = {t.dtype for t in ts if t is not None}
     if len(dts) != 1 or next(iter(dts)) not in _DT:
         raise TypeError(f"tensors must share one dtype of float32/bfloat16, got {dts}")
@@ -171,7 +174,7 @@ def _ptr(t):
 
 
 def _stream(t):
-    return torch.cuda.current_stream(t.device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _check(rc: int):

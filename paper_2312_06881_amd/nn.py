@@ -23,6 +23,7 @@ from __future__ import annotations
 import math
 
 import torch
+from torch.autograd import forward_ad
 
 from . import DyadError, backward_dw, backward_dx, forward
 
@@ -52,6 +53,16 @@ class _DyadLinearFn(torch.autograd.Function):
         if any(ctx.needs_input_grad[1:4]):
             dw1, dw2, db = backward_dw(dy, x, w1.shape[0], ctx.variant, want_db=ctx.has_bias)
         return dx, dw1, dw2, db, None, None
+
+
+def _plain(*ts):
+    """Whether a call records nothing and may skip autograd: gradients are off, no forward-mode
+    level, functorch transform or tracer is active, and every argument is a plain tensor."""
+    if torch.is_grad_enabled() or forward_ad._current_level >= 0 or torch._C._are_functorch_transforms_active():
+        return False
+    if torch.compiler.is_compiling() or torch.jit.is_tracing():
+        return False
+    return all(t is None or type(t) in (torch.Tensor, torch.nn.Parameter) for t in ts)
 
 
 _REFUSED = (-2, -4)   # DYAD_ERR_SHAPE, DYAD_ERR_DTYPE: no fused kernel for this layer
@@ -123,7 +134,10 @@ def dyad_linear(x, w1, w2, bias=None, variant="IT", out_features=None):
     D, bo, _ = w1.shape
     if out_features is None:
         out_features = bias.shape[0] if bias is not None else D * bo
-    y = _DyadLinearFn.apply(_tokens(x), w1, w2, bias, variant, out_features)
+    if _plain(x, w1, w2, bias):
+        y = forward(_tokens(x), w1, w2, bias, variant, n_out=out_features)
+    else:
+        y = _DyadLinearFn.apply(_tokens(x), w1, w2, bias, variant, out_features)
     return y.reshape(*x.shape[:-1], out_features)
 
 
@@ -135,7 +149,13 @@ def dyad_ff(x, fc1, fc2, variant="IT", ffn=None, fused=False):
     d = x.shape[-1]
     if ffn is None:
         ffn = fc1[0].shape[0] * fc1[0].shape[1]
-    y = _DyadFFFn.apply(_tokens(x), *fc1, *fc2, _variant_pair(variant), ffn, d, bool(fused))
+    pair = _variant_pair(variant)
+    if not fused and _plain(x, *fc1, *fc2):
+        # nothing to stash for a backward pass: the pre-activation is not written
+        a = forward(_tokens(x), *fc1, pair[0], act="gelu", n_out=ffn)
+        y = forward(a, *fc2, pair[1], n_out=d)
+    else:
+        y = _DyadFFFn.apply(_tokens(x), *fc1, *fc2, pair, ffn, d, bool(fused))
     return y.reshape(*x.shape[:-1], d)
 
 
