@@ -53,8 +53,9 @@ inline bool gemm_split_ws(const GemmPass &p, int splits, hipStream_t s, GemmArgs
     return true;
 }
 
+// splits: of the reduction (0: gemm_splits decides).
 template <int BM, int BN, int WGM, int WGN, int D, bool IN_T, bool OUT_T, bool W_T, int PF = 1, bool GELU_IN = false>
-hipError_t launch_tile(const GemmPass &p, hipStream_t s) {
+hipError_t launch_tile(const GemmPass &p, hipStream_t s, int splits = 0) {
     using C = GemmCfg<BM, BN, WGM, WGN, D, IN_T, OUT_T, W_T>;
     GemmArgs a{};
     // buffer offsets are 32-bit: one token panel of the input and of the output,
@@ -77,7 +78,7 @@ hipError_t launch_tile(const GemmPass &p, hipStream_t s) {
     if (tiles_m * tiles_n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     a.tiles_n = (int)tiles_n;
     a.tiles_total = (int)(tiles_m * tiles_n);
-    gemm_split_ws(p, gemm_splits(p, a.tiles_total, PF), s, a);
+    gemm_split_ws(p, splits > 0 ? splits : gemm_splits(p, a.tiles_total, PF), s, a);
     dyad_gemm_mfma<BM, BN, WGM, WGN, D, IN_T, OUT_T, W_T, occupancy<C>(), PF, GELU_IN>
         <<<a.tiles_total * a.splits, C::kThreads, 0, s>>>(a);
     hipError_t e = hipGetLastError();
@@ -338,6 +339,50 @@ hipError_t launch_permuted(const GemmPass &p, hipStream_t s) {
     }
 }
 
+// The 4-wave tile and reduction splits of a pass, largest tile first:
+//   - a tile that gives the GPU 256 workgroups by itself (384 where the
+//     reduction is short, under 12 stages a component, and the epilogue wants a
+//     second workgroup on the CU to hide behind; 128 at n_dyad 8 and 16 with an
+//     input transpose, where every column tile reads whole spans of the input);
+//   - untransposed weights: 64 x 64 alone from 192, then the largest tile that
+//     reaches 192 with up to 4 splits of at least 4 stages;
+//   - weights read transposed: the largest tile that reaches 144 alone or 192
+//     with up to 4 splits (narrow tiles leave most threads without a weight
+//     block to transpose), then 64 x 64 alone;
+//   - else 64 x 64 with up to 8 splits.
+// Measured on gfx950 over 1 to 4096 tokens against the largest tile that
+// fits, which left up to 7/8 of the CUs idle: OPT-125m fc2 forward 42 -> 12 us
+// at 256 tokens, 41 -> 24 at 2047 (64 x 64), 42 -> 31 at 4096 (64 x 192); fc1
+// input gradient of Dyad-IT 44 -> 26 at 2047 (128 x 192, 4 splits); 8192 ->
+// 2048, n_dyad 4, 512 tokens 47 -> 32 (128 x 128, 4 splits).
+struct TileChoice {
+    int bm = 0, bn = 0, splits = 1;
+    int rank = 0;
+
+    void consider(const GemmPass &p, int tm, int tn) {
+        if (p.bn % tn != 0) return;
+        const int64_t tiles = (p.M + tm - 1) / tm * (p.Nout / tn);
+        const int ks = (int)(p.bk / kStageK);
+        const bool smallest = tm == 64 && tn == 64;
+        const int enough = p.D >= 8 && p.in_t ? 128 : ks < 12 ? 384 : p.w_t ? 144 : 256;
+        int r = 1, sp = 1;
+        if (tiles >= enough && !(smallest && p.w_t)) {
+            r = 4;
+        } else if (smallest && tiles >= 192) {
+            r = p.w_t ? 2 : 3;
+        } else {
+            for (int k = 2; k <= 8 && tiles * sp < 192; ++k)
+                if (ks % k == 0 && ks / k >= 4 && (int64_t)k * p.M * p.Nout * 4 <= ((int64_t)64 << 20)) sp = k;
+            if (tiles * sp >= 192 && sp <= 4) r = p.w_t ? 4 : 2;
+        }
+        // ties go to the earlier, larger tile, except that the smallest is
+        // taken where none reaches 192 workgroups
+        if (r > rank || (r == 1 && rank == 1)) {
+            bm = tm; bn = tn; splits = sp; rank = r;
+        }
+    }
+};
+
 template <int D, bool IN_T, bool OUT_T, bool W_T>
 hipError_t dispatch_tiles(const GemmPass &p, hipStream_t s) {
     if (p.bk % kStageK != 0) return hipErrorNotSupported;
@@ -426,18 +471,29 @@ hipError_t dispatch_tiles(const GemmPass &p, hipStream_t s) {
             const hipError_t e = launch_components<D, IN_T, OUT_T, W_T>(p, s);
             if (e != hipErrorNotSupported) return e;
         }
-    constexpr int BM = D >= 8 ? 64 : 128;
-    // with an output transpose a 128 x 256 tile's D slabs need one workgroup per
-    // CU; 64 x 256 keeps two, which measures faster
-    constexpr int BM256 = OUT_T ? 64 : BM;
-    if constexpr (D < 16 && tile_ok<BM256, 256, 2, 2, D, OUT_T>())
-        if (p.bn % 256 == 0) return launch_tile<BM256, 256, 2, 2, D, IN_T, OUT_T, W_T>(p, s);
-    if constexpr (tile_ok<BM, 192, 2, 2, D, OUT_T>())
-        if (p.bn % 192 == 0) return launch_tile<BM, 192, 2, 2, D, IN_T, OUT_T, W_T>(p, s);
-    if constexpr (tile_ok<BM, 128, 2, 2, D, OUT_T>())
-        if (p.bn % 128 == 0) return launch_tile<BM, 128, 2, 2, D, IN_T, OUT_T, W_T>(p, s);
-    if constexpr (tile_ok<BM, 64, 2, 2, D, OUT_T>())
-        if (p.bn % 64 == 0) return launch_tile<BM, 64, 2, 2, D, IN_T, OUT_T, W_T>(p, s);
+    // 4-wave tiles, largest first (an output transpose's D slabs let only
+    // 64 x 256 run twice per CU; n_dyad 8 and 16 keep 64 tokens for the same reason)
+    TileChoice t;
+    const auto each = [&](auto try_tile) {
+        constexpr bool low = D < 8;
+        if constexpr (low && !OUT_T) try_tile(std::integral_constant<int, 128>{}, std::integral_constant<int, 256>{});
+        if constexpr ((!low || OUT_T) && D < 16) try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 256>{});
+        if constexpr (low) try_tile(std::integral_constant<int, 128>{}, std::integral_constant<int, 192>{});
+        if constexpr (low) try_tile(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{});
+        try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 192>{});
+        try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 128>{});
+        try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 64>{});
+    };
+    each([&](auto bm, auto bn) {
+        if constexpr (tile_ok<decltype(bm)::value, decltype(bn)::value, 2, 2, D, OUT_T>()) t.consider(p, bm, bn);
+    });
+    hipError_t e4 = hipErrorNotSupported;
+    each([&](auto bm, auto bn) {
+        if constexpr (tile_ok<decltype(bm)::value, decltype(bn)::value, 2, 2, D, OUT_T>())
+            if (t.bm == bm && t.bn == bn)
+                e4 = launch_tile<decltype(bm)::value, decltype(bn)::value, 2, 2, D, IN_T, OUT_T, W_T>(p, s, t.splits);
+    });
+    if (t.bm > 0) return e4;
     // An output transpose whose blocks are too narrow for any tile above
     // (n_dyad 16 with blocks of 64 or 128 columns): the components run apart.
     if constexpr (OUT_T) return launch_components<D, IN_T, OUT_T, W_T>(p, s);

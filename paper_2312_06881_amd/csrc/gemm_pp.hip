@@ -83,13 +83,13 @@ static bool res_columns(const GemmPass &p) {
 // blocks wide enough, for the faster multiply to earn that back.  Measured on
 // gfx950 per call against those, M = 2048 to 16384 tokens:
 //   no output transpose: n_dyad 8 from blocks of 256 1.35-2.1x (2048 -> 8192,
-//     8192 tokens: 242 -> 120 us; below, 768 -> 3072 0.9x), n_dyad 16
+//     8192 tokens: 242 -> 120 us; under 2560 tokens from 512, below 0.9-1.05x), n_dyad 16
 //     1.2-1.7x; n_dyad 2 and 4 from blocks of 512 both ways 1.2-1.6x (4096 ->
 //     4096, n_dyad 4: 187 -> 149 us; blocks of 256 0.8x).
 //   output transpose, residue-major: n_dyad 8 and 16 from reduction blocks of
 //     256 1.1-1.5x without a stashed pre-activation or GELU' (whose extra
-//     copies take the gain: 0.85-1.0x); n_dyad 2 and 4 from 512 (with an input
-//     copy as well from 1024) 1.04-1.6x (4096 -> 4096, n_dyad 4: 241 -> 153 us).
+//     copies take the gain: 0.85-1.0x); n_dyad 4 from 512 (with an input copy as
+//     well, and at n_dyad 2, from 1024) 1.04-1.6x (4096 -> 4096, n_dyad 4: 241 -> 153 us).
 //   output transpose, slice: n_dyad 8 from reduction blocks of 512 and output
 //     blocks of 256 1.4-1.7x (8192 -> 2048: 196 -> 118 us), n_dyad 2 and 4
 //     without an input copy from 1024 1.15-1.25x; n_dyad 16 0.9-1.0x.
@@ -100,13 +100,13 @@ bool pp_pays(const GemmPass &p) {
     const bool h = p.h_out != nullptr || p.epilogue == kEpiGeluGrad;
     const bool res = res_columns(p);
     if (p.D >= 8) {
-        if (!p.out_t) return p.D >= 16 || p.bk >= 256;
+        if (!p.out_t) return p.D >= 16 || p.bk >= 512 || (p.bk >= 256 && p.M >= 2560);
         if (res) return !h && p.bk >= 256;
         return p.D == 8 && p.bn >= 256 && p.bk >= 512;
     }
     if ((p.M + 255) / 256 * (p.Nout / 256) < 192) return false;
     if (!p.out_t) return p.bk >= 512 && p.bn >= 512;
-    if (res) return !h && p.bk >= (p.in_t ? 1024 : 512);
+    if (res) return !h && p.bk >= (p.in_t || p.D == 2 ? 1024 : 512);
     return !p.in_t && p.bn >= 256 && p.bk >= 1024;
 }
 
