@@ -155,9 +155,12 @@ constexpr int64_t pad_up(int64_t v, int64_t q) { return (v + q - 1) / q * q; }
 // for k < b and a source column below W, else 0 (either output may be null).
 hipError_t launch_pad_rows(const uint16_t *src, int64_t M, int64_t W, int D, int64_t b, int64_t bp,
                            uint16_t *dst1, uint16_t *dst2, hipStream_t s);
-// dst[g][r][c] = src[g][r][c] for r < R and c < C, else 0 (dst is D x Rp x Cp).
-hipError_t launch_pad_matrix(const uint16_t *src, int64_t D, int64_t R, int64_t C, int64_t Rp, int64_t Cp,
-                             uint16_t *dst, hipStream_t s);
+// dst1 / dst2 [D][Rp][Cp]: the D blocks of R x C of src1 / src2 in zeros, the
+// outputs (rows with by_row, else columns) of block g shifted where shift1 /
+// shift2 is set so that 8-output pieces keep the alignment of the real row.
+hipError_t launch_pad_weights(const uint16_t *src1, const uint16_t *src2, int64_t D, int64_t R, int64_t C, int64_t Rp,
+                              int64_t Cp, uint16_t *dst1, uint16_t *dst2, bool by_row, bool shift1, bool shift2,
+                              hipStream_t s);
 // dW1 / dW2 [D][bo][bi] and db [n_out] (nullable) from their padded forms
 // [D][bop][bip] and [D * bop].
 hipError_t launch_unpad_dw(const uint16_t *p1, const uint16_t *p2, const uint16_t *pdb, int64_t D, int64_t bo,

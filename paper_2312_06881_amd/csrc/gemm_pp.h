@@ -53,8 +53,8 @@ __device__ __forceinline__ void swap_rows(uint32_t &a, uint32_t &b) {
     b = r.y;
 }
 
-// 16 bytes at any 2-byte aligned address.
-typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+// Zero columns in front of padded block g of b real columns.
+__host__ __device__ constexpr int pp_pad_shift(int64_t g, int64_t b) { return (int)(g * b & 7); }
 
 // Slice columns per residue that a tile of BN consecutive real columns touches,
 // and the pitch (floats) of a staged token row of all D residues.
@@ -75,9 +75,13 @@ __host__ __device__ constexpr int64_t pp_slice_pitch(int64_t D, int BN) {
 //          sits at the block-order place of the column (c % D) * bn + c / D,
 //          and the tile's share of the slice goes through LDS (pp_stage_slice),
 //          where the permuted reads are cheap.
-//   PAD:   zero-padded blocks: columns of the tile's block past the real width
-//          are dropped, real rows have a.Nout_r columns and pieces any 2-byte
-//          alignment.
+//   PAD:   zero-padded blocks: block g's a.bn_r real columns sit behind
+//          pp_pad_shift(g, a.bn_r) columns of zeros, which makes 8-column pieces
+//          aligned in the padded block aligned in the real row of a.Nout_r
+//          columns as well (16-byte pieces at 2-byte aligned addresses cost
+//          the OPT-125m n_dyad 5 GELU forward 82 us against 60).  Columns
+//          outside the real ones are dropped, element by element in the
+//          pieces at a block's ends.
 //   RES:   the tile's outputs are columns n0.. of residue-major rows; its real
 //          columns (for the bias) are c_real + a.D * t.
 template <class C, int BM, int BN, bool SLICE, bool ADD, bool PAD, bool RES>
@@ -104,12 +108,16 @@ __device__ __forceinline__ void pp_epilogue(const GemmArgs &a, unsigned char *sm
     const bool act = a.epilogue == kEpiBiasGelu;
     const bool keep_h = act && a.h_out != nullptr;
     const uint32_t Nr = (uint32_t)(PAD ? a.Nout_r : a.Nout);
-    const int cb = PAD ? g * (int)a.bn_r + jb : n0;       // real column of the tile's first
-    int nt = BN;                                           // real columns of the tile
+    // real column of the tile's first, and its real columns lo .. nt - 1
+    const int sh = PAD ? pp_pad_shift(g, a.bn_r) : 0;
+    const int cb = PAD ? g * (int)a.bn_r - sh + jb : n0;
+    const int lo = PAD && sh > jb ? sh - jb : 0;
+    int nt = BN;
     if constexpr (PAD) {
-        nt = (int)a.bn_r - jb < nt ? (int)a.bn_r - jb : nt;
+        nt = (int)a.bn_r + sh - jb < nt ? (int)a.bn_r + sh - jb : nt;
         nt = (int)Nr - cb < nt ? (int)Nr - cb : nt;
     }
+    const bool rows16 = !PAD || Nr % 8 == 0;               // pieces are 16-byte aligned
     const __amdgpu_buffer_rsrc_t rO = buffer_rsrc(a.out + m0 * Nr, rows_t * Nr * 2u);
     const uint16_t *hbase = grad ? a.h_in : a.h_out;
     const __amdgpu_buffer_rsrc_t rH = buffer_rsrc((hbase ? hbase : a.out) + m0 * Nr, rows_t * Nr * 2u);
@@ -125,53 +133,49 @@ __device__ __forceinline__ void pp_epilogue(const GemmArgs &a, unsigned char *sm
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int t = wn0 + 16 * j + 4 * lg + v;
-                if (!PAD || t < nt) bias[j][v] = bf16_to_f32(a.bias[RES ? c_real + (int)a.D * t : cb + t]);
+                if (!PAD || (t >= lo && t < nt)) bias[j][v] = bf16_to_f32(a.bias[RES ? c_real + (int)a.D * t : cb + t]);
             }
     }
     // this lane's 16-byte piece of a column block pair, after the row swap
     const int piece = (lg & 1) * 16 + (lg >> 1) * 8;
-    auto load_h = [&](int i, int jp) -> uint4 {
+    // default cache policy: a lane row's 64 bytes are half a line, which the L2
+    // completes (streamed, 8192 tokens of 4096 -> 4096 took 150 us against
+    // 142, and padded blocks, whose pieces straddle lines, 122 against 92)
+    constexpr int kStore = 0;
+    // WHOLE: every column of the tile is real and pieces are 16-byte aligned
+    auto load_h = [&](auto whole, int i, int jp) -> uint4 {
         const uint32_t row = (uint32_t)(wm0 + 16 * i + lr);
         const int t = wn0 + 32 * jp + piece;
         uint4 h = make_uint4(0u, 0u, 0u, 0u);
-        if constexpr (!PAD) {
+        if (decltype(whole)::value || (rows16 && t >= lo && t + 8 <= nt)) {
             h = bload16_stream(rH, (row * Nr + (uint32_t)(cb + t)) * 2u, 0);
         } else if (row < rows_t) {
             const uint16_t *src = a.h_in + (m0 + row) * (int64_t)Nr + cb + t;
-            if (t + 8 <= nt) {
-                const u32x4_any_t w = *reinterpret_cast<const u32x4_any_t *>(src);
-                h = make_uint4(w.x, w.y, w.z, w.w);
-            } else {
-                uint16_t e[8];
+            uint16_t e[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) e[k] = t + k < nt ? src[k] : (uint16_t)0;
-                h = make_uint4(e[0] | (uint32_t)e[1] << 16, e[2] | (uint32_t)e[3] << 16, e[4] | (uint32_t)e[5] << 16,
-                               e[6] | (uint32_t)e[7] << 16);
-            }
+            for (int k = 0; k < 8; ++k) e[k] = t + k >= lo && t + k < nt ? src[k] : (uint16_t)0;
+            h = make_uint4(e[0] | (uint32_t)e[1] << 16, e[2] | (uint32_t)e[3] << 16, e[4] | (uint32_t)e[5] << 16,
+                           e[6] | (uint32_t)e[7] << 16);
         }
         swap_rows(h.x, h.z);
         swap_rows(h.y, h.w);
         return h;
     };
-    auto store = [&](const __amdgpu_buffer_rsrc_t &r, uint16_t *base, int i, int jp, const float (&x)[8]) {
+    auto store = [&](auto whole, const __amdgpu_buffer_rsrc_t &r, uint16_t *base, int i, int jp, const float (&x)[8]) {
         uint32_t d0 = pack_bf16(x[0], x[1]), d1 = pack_bf16(x[2], x[3]);
         uint32_t s0 = pack_bf16(x[4], x[5]), s1 = pack_bf16(x[6], x[7]);
         swap_rows(d0, s0);
         swap_rows(d1, s1);
         const uint32_t row = (uint32_t)(wm0 + 16 * i + lr);
         const int t = wn0 + 32 * jp + piece;
-        if constexpr (!PAD) {
-            bstore16(r, (row * Nr + (uint32_t)(cb + t)) * 2u, make_uint4(d0, d1, s0, s1));
+        if (decltype(whole)::value || (rows16 && t >= lo && t + 8 <= nt)) {
+            bstore16<kStore>(r, (row * Nr + (uint32_t)(cb + t)) * 2u, make_uint4(d0, d1, s0, s1));
         } else if (row < rows_t) {
             uint16_t *dst = base + (m0 + row) * (int64_t)Nr + cb + t;
-            if (t + 8 <= nt) {
-                *reinterpret_cast<u32x4_any_t *>(dst) = u32x4_any_t{d0, d1, s0, s1};
-            } else {
-                const uint32_t w[4] = {d0, d1, s0, s1};
+            const uint32_t w[4] = {d0, d1, s0, s1};
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (t + k < nt) dst[k] = (uint16_t)(w[k >> 1] >> (16 * (k & 1)));
-            }
+            for (int k = 0; k < 8; ++k)
+                if (t + k >= lo && t + k < nt) dst[k] = (uint16_t)(w[k >> 1] >> (16 * (k & 1)));
         }
     };
 
@@ -190,13 +194,25 @@ __device__ __forceinline__ void pp_epilogue(const GemmArgs &a, unsigned char *sm
                 at[j][v] = a.unperm ? c % D * span + c / D - tb : t;
             }
     }
-    const int rounds = ADD ? (C::kLds / 4) / (kRound * pitch) : SM;   // block rows staged at a time
+    auto slice_at = [&](int i, int j, int v) -> float {
+        const uint32_t row = (uint32_t)(wm0 + 16 * i + lr);
+        const int t = wn0 + 16 * j + 4 * lg + v, c = cb + t;
+        if (row >= rows_t || t < lo || t >= nt) return 0.f;
+        const int64_t col = a.unperm ? (int64_t)(c % D) * a.bn + c / D : (int64_t)n0 + t;
+        return a.part[((int64_t)a.slice0 * a.M + m0 + row) * a.Nout + col];
+    };
+    // block rows staged at a time; rows of so many residues that not even one
+    // fits are read in place
+    const int rounds = ADD ? (int)((int64_t)(C::kLds / 4) / ((int64_t)kRound * pitch)) : SM;
 
+    // two instances, so that the tiles inside a padded block (most of them)
+    // carry nothing of the piecemeal form
+    auto rows = [&](auto whole) {
 #pragma unroll
     for (int i = 0; i < SM; ++i) {
         const float *row_slice = nullptr;
         if constexpr (ADD) {
-            if (i % rounds == 0) {
+            if (rounds > 0 && i % rounds == 0) {
                 // stage block rows i .. i + rounds - 1 of every wave row
                 if (i > 0) __syncthreads();
                 const __amdgpu_buffer_rsrc_t rS =
@@ -224,12 +240,12 @@ __device__ __forceinline__ void pp_epilogue(const GemmArgs &a, unsigned char *sm
                 wait_vm<0>();
                 __syncthreads();
             }
-            row_slice = reinterpret_cast<const float *>(smem) + ((i % rounds) * kRound + wm0 / C::WM * 16 + lr) * pitch;
+            if (rounds > 0) row_slice = reinterpret_cast<const float *>(smem) + ((i % rounds) * kRound + wm0 / C::WM * 16 + lr) * pitch;
         }
         uint4 h[SN / 2];
         if (grad) {
 #pragma unroll
-            for (int jp = 0; jp < SN / 2; ++jp) h[jp] = load_h(i, jp);
+            for (int jp = 0; jp < SN / 2; ++jp) h[jp] = load_h(whole, i, jp);
         }
 #pragma unroll
         for (int jp = 0; jp < SN / 2; ++jp) {
@@ -238,7 +254,10 @@ __device__ __forceinline__ void pp_epilogue(const GemmArgs &a, unsigned char *sm
             for (int e = 0; e < 8; ++e) {
                 const int j = 2 * jp + (e >> 2), v = e & 3;
                 x[e] = acc[i][j][v];
-                if constexpr (ADD) x[e] += row_slice[at[j][v]];
+                if constexpr (ADD) {
+                    if (rounds > 0) x[e] += row_slice[at[j][v]];
+                    else x[e] += slice_at(i, j, v);
+                }
             }
             if (grad) {
 #pragma unroll
@@ -247,14 +266,17 @@ __device__ __forceinline__ void pp_epilogue(const GemmArgs &a, unsigned char *sm
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] += bias[2 * jp + (e >> 2)][e & 3];
                 if (act) {
-                    if (keep_h) store(rH, a.h_out, i, jp, x);
+                    if (keep_h) store(whole, rH, a.h_out, i, jp, x);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[e] = gelu(x[e]);
                 }
             }
-            store(rO, a.out, i, jp, x);
+            store(whole, rO, a.out, i, jp, x);
         }
     }
+    };
+    if (!PAD || (rows16 && lo == 0 && nt == BN)) rows(std::true_type{});
+    else if constexpr (PAD) rows(std::false_type{});
 }
 
 template <int BM, int BN, int WGM, int WGN, bool W_T, int FORM>
@@ -386,15 +408,8 @@ inline bool pp_fits(const GemmArgs &a, int BM) {
 
 template <int BM, int BN, int WGM, int WGN, bool W_T, int FORM>
 hipError_t launch_pp_tile(GemmArgs a, hipStream_t s) {
-    using C = PPCfg<BM, BN, WGM, WGN, W_T>;
     const int64_t tiles_m = (a.M + BM - 1) / BM, tiles_n = a.Nout / BN;
     if (FORM == kPPRes && (a.bn % a.D != 0 || a.bn / a.D % BN != 0)) return hipErrorNotSupported;
-    // a permuted slice is staged at least one block row of all waves at a time
-    if ((FORM == kPPAdd || FORM == kPPPadAdd) && a.unperm &&
-        pp_slice_pitch(a.D, BN) * (16 * WGM) * 4 > (int64_t)C::kLds)
-        return hipErrorNotSupported;
-    if (a.bn % BN != 0 || a.bk % kStageK != 0 || !pp_fits(a, BM) || tiles_m * tiles_n >= ((int64_t)1 << 31))
-        return hipErrorNotSupported;
     a.tiles_n = (int)tiles_n;
     a.tiles_total = (int)(tiles_m * tiles_n);
     a.splits = 1;

@@ -5,14 +5,25 @@
 namespace dyad {
 namespace {
 
+// The tile of a launch: columns in a run of w (an output block, or one block
+// and residue).  256-wide rows of the output fill the matrix cores best where
+// they fill the GPU.  Two workgroups of the tiles under 128 x 128 share a CU
+// and hide each other's epilogues, which wins for short reductions and for
+// slices staged through LDS (768 -> 3072, n_dyad 5, 8192 tokens, GELU forward:
+// pair 92 -> 83 us, slice 171 -> 143; 3072 -> 768 at 640 a block 76 -> 72 the
+// other way; 8192 -> 32768, n_dyad 16, 4096 tokens, 512 a block 495 -> 529).
 template <bool W_T, int FORM>
 hipError_t launch_form(const GemmArgs &a, hipStream_t s) {
     const int64_t tm = (a.M + 255) / 256;
-    const int64_t w = FORM == kPPRes && a.bn % a.D == 0 ? a.bn / a.D : a.bn;   // a tile's columns lie in a run of w
-    if (w % 256 == 0 && tm * (a.Nout / 256) >= 192) return launch_pp_tile<256, 256, 2, 4, W_T, FORM>(a, s);
-    if (w % 192 == 0 && tm * (a.Nout / 192) >= 192) return launch_pp_tile<256, 192, 4, 2, W_T, FORM>(a, s);
-    if (w % 128 == 0 && tm * (a.Nout / 128) >= 192) return launch_pp_tile<256, 128, 4, 2, W_T, FORM>(a, s);
-    if (w % 128 == 0) return launch_pp_tile<128, 128, 2, 4, W_T, FORM>(a, s);
+    const int64_t w = FORM == kPPRes && a.bn % a.D == 0 ? a.bn / a.D : a.bn;
+    const bool add = FORM == kPPAdd || FORM == kPPPadAdd;
+    auto fills = [&](int bn) { return tm * (a.Nout / bn) >= 192; };
+    if (w % 256 == 0 && fills(256)) return launch_pp_tile<256, 256, 2, 4, W_T, FORM>(a, s);
+    if (w % 192 == 0 && fills(192)) return launch_pp_tile<256, 192, 4, 2, W_T, FORM>(a, s);
+    if (w % 128 == 0 && (add || a.bk < 512 || !fills(128))) return launch_pp_tile<128, 128, 2, 4, W_T, FORM>(a, s);
+    if (w % 128 == 0) return launch_pp_tile<256, 128, 4, 2, W_T, FORM>(a, s);
+    if (w % 64 == 0 && ((add && W_T) || (!add && a.bk < 512) || !fills(64)))
+        return launch_pp_tile<128, 64, 4, 2, W_T, FORM>(a, s);
     if (w % 64 == 0) return launch_pp_tile<256, 64, 4, 2, W_T, FORM>(a, s);
     return hipErrorNotSupported;
 }

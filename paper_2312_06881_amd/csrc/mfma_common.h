@@ -204,9 +204,10 @@ __device__ __forceinline__ uint4 gelu8(uint4 v) {
 constexpr int kStreamPolicy = 2;
 
 // 16 bytes to base + voff, streamed; dropped when voff lies past the buffer's range.
+template <int POLICY = kStreamPolicy>
 __device__ __forceinline__ void bstore16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint4 v) {
     const u32x4_t w = {v.x, v.y, v.z, v.w};
-    __builtin_amdgcn_raw_buffer_store_b128(w, r, (int)voff, 0, kStreamPolicy);
+    __builtin_amdgcn_raw_buffer_store_b128(w, r, (int)voff, 0, POLICY);
 }
 
 // 16 bytes at base + voff + soff read once (streamed); zero past the buffer's range.

@@ -58,14 +58,23 @@ hipError_t launch_pad_rows(const uint16_t *src, int64_t M, int64_t W, int D, int
     return hipGetLastError();
 }
 
-// Zero-padded copy of D blocks of R x C (rows of C) as blocks of Rp x Cp.
-__global__ void __launch_bounds__(256) pad_matrix_kernel(const uint16_t *src, int64_t D, int R, int C, int Rp,
-                                                         int Cp, uint16_t *dst) {
+// Zero-padded copies of the two weight tensors (grid y: component), D blocks of
+// R x C (rows of C) as blocks of Rp x Cp.  The block's rows (by_row) or
+// columns are outputs; where a component's shift is set, block g's start at
+// pp_pad_shift(g, outputs).
+__global__ void __launch_bounds__(256) pad_weights_kernel(const uint16_t *src1, const uint16_t *src2, int64_t D, int R,
+                                                          int C, int Rp, int Cp, uint16_t *dst1, uint16_t *dst2,
+                                                          int by_row, int shift1, int shift2) {
+    const uint16_t *src = blockIdx.y ? src2 : src1;
+    uint16_t *dst = blockIdx.y ? dst2 : dst1;
+    const bool shift = blockIdx.y ? shift2 : shift1;
     const int64_t units = D * Rp * (Cp / 8);
     for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < units; u += (int64_t)gridDim.x * 256) {
         const int64_t g = u / ((int64_t)Rp * (Cp / 8));
         const int rem = (int)(u - g * Rp * (Cp / 8));
-        const int r = rem / (Cp / 8), c0 = (rem % (Cp / 8)) * 8;
+        const int rp = rem / (Cp / 8), cp = (rem % (Cp / 8)) * 8;
+        const int sh = shift ? pp_pad_shift(g, by_row ? R : C) : 0;
+        const int r = by_row ? rp - sh : rp, c0 = by_row ? cp : cp - sh;
         uint32_t w[4];
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
@@ -73,23 +82,25 @@ __global__ void __launch_bounds__(256) pad_matrix_kernel(const uint16_t *src, in
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int c = c0 + 2 * h + e;
-                const uint32_t v = (r < R && c < C) ? (uint32_t)src[(g * R + r) * C + c] : 0u;
+                const uint32_t v = (r >= 0 && r < R && c >= 0 && c < C) ? (uint32_t)src[(g * R + r) * C + c] : 0u;
                 pair |= v << (16 * e);
             }
             w[h] = pair;
         }
-        *reinterpret_cast<uint4 *>(dst + (g * Rp + r) * Cp + c0) = make_uint4(w[0], w[1], w[2], w[3]);
+        *reinterpret_cast<uint4 *>(dst + (g * Rp + rp) * Cp + cp) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
 
-hipError_t launch_pad_matrix(const uint16_t *src, int64_t D, int64_t R, int64_t C, int64_t Rp, int64_t Cp,
-                             uint16_t *dst, hipStream_t s) {
+hipError_t launch_pad_weights(const uint16_t *src1, const uint16_t *src2, int64_t D, int64_t R, int64_t C, int64_t Rp,
+                              int64_t Cp, uint16_t *dst1, uint16_t *dst2, bool by_row, bool shift1, bool shift2,
+                              hipStream_t s) {
     if (Cp % 8 != 0 || R > Rp || C > Cp || Rp * Cp >= ((int64_t)1 << 31)) return hipErrorNotSupported;
     const int64_t units = D * Rp * (Cp / 8);
     if (units == 0) return hipSuccess;
     int64_t grid = (units + 255) / 256;
     if (grid > 4096) grid = 4096;
-    pad_matrix_kernel<<<(unsigned)grid, 256, 0, s>>>(src, D, (int)R, (int)C, (int)Rp, (int)Cp, dst);
+    pad_weights_kernel<<<dim3((unsigned)grid, 2), 256, 0, s>>>(src1, src2, D, (int)R, (int)C, (int)Rp, (int)Cp, dst1,
+                                                              dst2, by_row, shift1, shift2);
     return hipGetLastError();
 }
 

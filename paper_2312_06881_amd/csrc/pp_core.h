@@ -127,26 +127,31 @@ __device__ __forceinline__ void pp_barrier() {
 #define PP_OTB(i) [bl##i] "=&v"(bl[i]), [bh##i] "=&v"(bh[i])
 #define PP_IA(i) [pa##i] "v"(pa[i])
 #define PP_IB(i) [pb##i] "v"(pb[i])
+#define PP_RA2 PP_RA(0, 0) PP_RA(1, 2048)
 #define PP_RA4 PP_RA(0, 0) PP_RA(1, 2048) PP_RA(2, 4096) PP_RA(3, 6144)
 #define PP_RA8 PP_RA4 PP_RA(4, 8192) PP_RA(5, 10240) PP_RA(6, 12288) PP_RA(7, 14336)
 #define PP_RB2 PP_RB(0, 0) PP_RB(1, 2048)
 #define PP_RB4 PP_RB2 PP_RB(2, 4096) PP_RB(3, 6144)
 #define PP_RB6 PP_RB4 PP_RB(4, 8192) PP_RB(5, 10240)
+#define PP_TA2 PP_TA(0) PP_TA(1)
 #define PP_TA4 PP_TA(0) PP_TA(1) PP_TA(2) PP_TA(3)
 #define PP_TA8 PP_TA4 PP_TA(4) PP_TA(5) PP_TA(6) PP_TA(7)
 #define PP_TB2 PP_TB(0) PP_TB(1)
 #define PP_TB4 PP_TB2 PP_TB(2) PP_TB(3)
 #define PP_TB6 PP_TB4 PP_TB(4) PP_TB(5)
+#define PP_OA2 PP_OA(0), PP_OA(1)
 #define PP_OA4 PP_OA(0), PP_OA(1), PP_OA(2), PP_OA(3)
 #define PP_OA8 PP_OA4, PP_OA(4), PP_OA(5), PP_OA(6), PP_OA(7)
 #define PP_OB2 PP_OB(0), PP_OB(1)
 #define PP_OB4 PP_OB2, PP_OB(2), PP_OB(3)
 #define PP_OB6 PP_OB4, PP_OB(4), PP_OB(5)
+#define PP_OTA2 PP_OTA(0), PP_OTA(1)
 #define PP_OTA4 PP_OTA(0), PP_OTA(1), PP_OTA(2), PP_OTA(3)
 #define PP_OTA8 PP_OTA4, PP_OTA(4), PP_OTA(5), PP_OTA(6), PP_OTA(7)
 #define PP_OTB2 PP_OTB(0), PP_OTB(1)
 #define PP_OTB4 PP_OTB2, PP_OTB(2), PP_OTB(3)
 #define PP_OTB6 PP_OTB4, PP_OTB(4), PP_OTB(5)
+#define PP_IA2 PP_IA(0), PP_IA(1)
 #define PP_IA4 PP_IA(0), PP_IA(1), PP_IA(2), PP_IA(3)
 #define PP_IA8 PP_IA4, PP_IA(4), PP_IA(5), PP_IA(6), PP_IA(7)
 #define PP_IB2 PP_IB(0), PP_IB(1)
@@ -184,7 +189,9 @@ __device__ __forceinline__ void pp_read(const uint32_t (&pa)[TA ? SM : 1], const
     PP_CASE(4, 6)
     PP_CASE(4, 4)
     PP_CASE(4, 2)
-    static_assert((SM == 8 && SN == 4) || (SM == 4 && (SN == 6 || SN == 4 || SN == 2)), "a fragment read exists");
+    PP_CASE(2, 2)
+    static_assert((SM == 8 && SN == 4) || (SM == 4 && (SN == 6 || SN == 4 || SN == 2)) || (SM == 2 && SN == 2),
+                  "a fragment read exists");
     if constexpr (TA) {
 #pragma unroll
         for (int i = 0; i < SM; ++i) a[i] = __builtin_shufflevector(al[i], ah[i], 0, 1, 2, 3, 4, 5, 6, 7);
