@@ -1,6 +1,6 @@
 // General kernels: any n_dyad, any block sizes, widths that n_dyad does not
-// divide (zero-padded), both dtypes.  The fp32 path and every shape the MFMA
-// kernels do not cover use them.  Arithmetic is fp32 FMA on the vector ALUs,
+// divide (zero-padded), both dtypes.  Every shape the matrix-core kernels do
+// not cover uses them.  Arithmetic is fp32 FMA on the vector ALUs,
 // tiled through LDS.
 //
 // Grouped GEMM (forward and input gradient).  The output columns of a pass
