@@ -142,8 +142,9 @@ inline bool permuted_pays(int D, bool out_t, bool w_t, int64_t M, int64_t bk) {
     return bk >= 512;
 }
 
-// The same form on the large tiles of gemm_pp.h, in token chunks.
-bool pp_pays(const GemmPass &p);
+// The same form on the large tiles of gemm_pp.h, in token chunks, for a pass
+// that pp_pays (pp_plan.h) admits; hipErrorNotSupported, launching nothing,
+// without a workspace.
 hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s);
 
 // Zero-padded forms (padded_mfma.h): block-ordered copies padded to whole

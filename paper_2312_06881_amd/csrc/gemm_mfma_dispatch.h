@@ -3,6 +3,7 @@
 
 #include "gemm_mfma.h"
 #include "gemm_mfma2.h"
+#include "pp_plan.h"
 
 namespace dyad {
 

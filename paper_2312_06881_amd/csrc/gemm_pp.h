@@ -23,6 +23,7 @@
 
 #include "gemm_common.h"
 #include "pp_core.h"
+#include "pp_plan.h"
 
 namespace dyad {
 
@@ -400,15 +401,11 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
                                                                wn0, g * bn + r + D * t0);
 }
 
-// Whether the tile's 32-bit offsets reach all of it.
-inline bool pp_fits(const GemmArgs &a, int BM) {
-    const int64_t lim = (int64_t)1 << 31;
-    return (int64_t)BM * a.Kin * 2 < lim && (int64_t)BM * a.Nout * 4 < lim && 2 * a.D * a.bn * a.bk < lim;
-}
-
 template <int BM, int BN, int WGM, int WGN, bool W_T, int FORM>
 hipError_t launch_pp_tile(GemmArgs a, hipStream_t s) {
     const int64_t tiles_m = (a.M + BM - 1) / BM, tiles_n = a.Nout / BN;
+    if (!pp_fits(BM, a.Kin, a.Nout, a.D * a.bn * a.bk) || tiles_m * tiles_n >= ((int64_t)1 << 31))
+        return hipErrorNotSupported;
     if (FORM == kPPRes && (a.bn % a.D != 0 || a.bn / a.D % BN != 0)) return hipErrorNotSupported;
     a.tiles_n = (int)tiles_n;
     a.tiles_total = (int)(tiles_m * tiles_n);

@@ -1,6 +1,7 @@
 // Tile choice and instances of the grouped GEMM on block-ordered operands
 // (gemm_pp.h).
 #include "gemm_pp.h"
+#include "pp_plan.h"
 
 namespace dyad {
 namespace {
@@ -80,47 +81,6 @@ hipError_t launch_interleave(const uint16_t *in, uint16_t *out, int64_t M, int64
     return hipGetLastError();
 }
 
-// Residue-major columns in whole tiles: every (block, residue) pair of the
-// output holds a multiple of 128 or 192 columns (64-column tiles lost to the
-// slice: n_dyad 8, 4096 tokens, 16384 -> 4096 input gradient with 64 columns
-// a pair 397 against 299 us).
-static bool res_columns(const GemmPass &p) {
-    return p.out_t && p.bn % p.D == 0 && (p.bn / p.D % 128 == 0 || p.bn / p.D % 192 == 0);
-}
-
-// Whether a pass takes the plain-block form on the large tiles rather than
-// the fused tiles (or, at n_dyad 16, the earlier plain-block tiles).  The form
-// pays for its copies in HBM traffic, so it wants reductions long enough, and
-// blocks wide enough, for the faster multiply to earn that back.  Measured on
-// gfx950 per call against those, M = 2048 to 16384 tokens:
-//   no output transpose: n_dyad 8 from blocks of 256 1.35-2.1x (2048 -> 8192,
-//     8192 tokens: 242 -> 120 us; under 2560 tokens from 512, below 0.9-1.05x), n_dyad 16
-//     1.2-1.7x; n_dyad 2 and 4 from blocks of 512 both ways 1.2-1.6x (4096 ->
-//     4096, n_dyad 4: 187 -> 149 us; blocks of 256 0.8x).
-//   output transpose, residue-major: n_dyad 8 and 16 from reduction blocks of
-//     256 1.1-1.5x without a stashed pre-activation or GELU' (whose extra
-//     copies take the gain: 0.85-1.0x); n_dyad 4 from 512 (with an input copy as
-//     well, and at n_dyad 2, from 1024) 1.04-1.6x (4096 -> 4096, n_dyad 4: 241 -> 153 us).
-//   output transpose, slice: n_dyad 8 from reduction blocks of 512 and output
-//     blocks of 256 1.4-1.7x (8192 -> 2048: 196 -> 118 us), n_dyad 2 and 4
-//     without an input copy from 1024 1.15-1.25x; n_dyad 16 0.9-1.0x.
-// n_dyad 2 and 4 also want 192 tiles of 256 x 256: with fewer, the fused
-// tiles' smaller ones fill the GPU better (0.94x at 128 tiles).
-bool pp_pays(const GemmPass &p) {
-    if (p.M <= 1024 || p.bk % kStageK != 0 || p.bn % 64 != 0) return false;
-    const bool h = p.h_out != nullptr || p.epilogue == kEpiGeluGrad;
-    const bool res = res_columns(p);
-    if (p.D >= 8) {
-        if (!p.out_t) return p.D >= 16 || p.bk >= 512 || (p.bk >= 256 && p.M >= 2560);
-        if (res) return !h && p.bk >= 256;
-        return p.D == 8 && p.bn >= 256 && p.bk >= 512;
-    }
-    if ((p.M + 255) / 256 * (p.Nout / 256) < 192) return false;
-    if (!p.out_t) return p.bk >= 512 && p.bn >= 512;
-    if (res) return !h && p.bk >= (p.in_t || p.D == 2 ? 1024 : 512);
-    return !p.in_t && p.bn >= 256 && p.bk >= 1024;
-}
-
 // Large batches with a transpose on plain blocks.  An input transpose first de-interleaves the input (residue
 // g's columns k*D + g become the contiguous block g).  Without an output
 // transpose both components then run in one loop (kPPPair).  With one:
@@ -141,7 +101,7 @@ constexpr size_t kPPChunkBytes = (size_t)160 << 20;
 hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s) {
     if (p.bk % kStageK != 0 || p.bn % 64 != 0) return hipErrorNotSupported;
     const int D = (int)p.D;
-    const bool res = res_columns(p);
+    const bool res = pp_res_columns(p);
     const bool slices = p.out_t && !res;
     const bool keep_h = res && p.epilogue == kEpiBiasGelu && p.h_out;
     const bool grad = res && p.epilogue == kEpiGeluGrad;
