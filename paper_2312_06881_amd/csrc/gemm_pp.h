@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
 #pragma unroll
     for (int q = 0; q < SA::kPer; ++q) {
         int row, byte;
-        const int i = pp_instr<BM, false>(wave, q);
+        const int i = pp_instr(wave, q);
         pp_source<BM, false>(i, lane, row, byte);
         voA[q] = (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)(g * bk) * 2u + (uint32_t)byte;
         if constexpr (kRes) voA2[q] = (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)(r * bk) * 2u + (uint32_t)byte;
@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
 #pragma unroll
     for (int q = 0; q < SB::kPer; ++q) {
         int row, byte;
-        const int i = pp_instr<BN, W_T>(wave, q);
+        const int i = pp_instr(wave, q);
         pp_source<BN, W_T>(i, lane, row, byte);
         if constexpr (kRes) {
             const int tg = g * (bn / D) + t0;             // weight row (column) of t = 0 in group r
@@ -345,6 +345,12 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
         else voB[q] = (uint32_t)(g * bn + jb + row) * (uint32_t)bk * 2u + (uint32_t)byte;
         loB[q] = (uint32_t)C::kOffB + 1024u * (uint32_t)i;
     }
+    // steps back of a one-step unit; a side's loads alternate waves, so without
+    // W_T one value serves all of them
+    const uint32_t backA = pp_back<BM, false>(wave, lane, 0u);
+    uint32_t backB[SB::kPer];
+#pragma unroll
+    for (int q = 0; q < SB::kPer; ++q) backB[q] = pp_back<BN, W_T>(W_T ? pp_instr(wave, q) : wave, lane, (uint32_t)bn * 2u);
     const uint32_t stepB = W_T ? (uint32_t)(kPPK * 2) * (uint32_t)bn : (uint32_t)(kPPK * 2);
     const int nk = (ks + 1) / 2;                   // units per component; the last may hold one step
     const int units = kPair ? 2 * nk : nk;
@@ -353,23 +359,28 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
         const int k = kPair ? d >> 1 : d;
         return (uint32_t)(k < nk ? k : nk - 1);
     };
+    auto both = [&](int d) { return 2 * (int)unit_k(d) + 1 < ks; };
     auto issue_a = [&](int d) {
         const __amdgpu_buffer_rsrc_t rs = kPair && (d & 1) ? rA2 : rA1;
         lds_u8 *slot = lds + d % C::kSlotA * SA::kBytes;
+        const bool one = !both(d);
 #pragma unroll
         for (int q = 0; q < SA::kPer; ++q) {
             uint32_t vo = voA[q];
             if constexpr (kRes) vo = d & 1 ? voA2[q] : vo;
+            vo -= one ? backA : 0u;
             dma16(rs, slot + loA[q], vo, unit_k(d) * (uint32_t)(kPPK * 2));
         }
     };
     auto issue_b = [&](int d) {
         const __amdgpu_buffer_rsrc_t rs = kPair && (d & 1) ? rW2 : rW1;
         lds_u8 *slot = lds + d % C::kSlotB * SB::kBytes;
+        const bool one = !both(d);
 #pragma unroll
         for (int q = 0; q < SB::kPer; ++q) {
             uint32_t vo = voB[q];
             if constexpr (kRes) vo = d & 1 ? voB2[q] : vo;
+            vo -= one ? backB[q] : 0u;
             dma16(rs, slot + loB[q], vo, unit_k(d) * stepB);
         }
     };
@@ -386,7 +397,6 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
         for (int j = 0; j < (W_T ? C::kSubN : 1); ++j)
             pb[j] = pp_step<BN, W_T>(fb[j] + (uint32_t)(d % C::kSlotB * SB::kBytes), h);
     };
-    auto both = [&](int d) { return 2 * (int)unit_k(d) + 1 < ks; };
 
     f32x4_t acc[C::kSubM][C::kSubN];
 #pragma unroll

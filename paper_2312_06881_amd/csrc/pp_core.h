@@ -48,24 +48,19 @@ template <int N, bool TR>
 struct PPSide {
     static constexpr int kPitch = TR ? round256(2 * N) : 2 * kPPK;
     static constexpr int kBytes = (TR ? kPPK : N) * kPitch;
-    static constexpr int kInstr = kBytes / 1024;                  // 1 KB wave loads
-    static constexpr int kPer = (kInstr + kPPWaves - 1) / kPPWaves;   // per wave (the last ones repeated)
-    static_assert(kBytes % 1024 == 0, "whole wave loads");
+    static constexpr int kInstr = kBytes / 1024;        // 1 KB wave loads
+    static constexpr int kPer = kInstr / kPPWaves;      // per wave
+    static_assert(kBytes % 1024 == 0 && kInstr % kPPWaves == 0, "whole wave loads, the same number for each wave");
 };
 
-// Wave load q of wave `wave`: its index (the last load again where the loads
-// do not divide by the waves: same bytes to the same place).
-template <int N, bool TR>
-__device__ __forceinline__ int pp_instr(int wave, int q) {
-    const int i = wave + kPPWaves * q;
-    return i < PPSide<N, TR>::kInstr ? i : PPSide<N, TR>::kInstr - 1;
-}
+// Wave load q of wave `wave`.
+__host__ __device__ constexpr int pp_instr(int wave, int q) { return wave + kPPWaves * q; }
 
 // Source of lane `lane` of wave load i: tile row (or reduction row with TR)
 // and the byte within that row.  (TR rows padded to 256 bytes: lanes in the
 // padding load column 0, which nothing reads.)
 template <int N, bool TR>
-__device__ __forceinline__ void pp_source(int i, int lane, int &row, int &byte) {
+__host__ __device__ __forceinline__ void pp_source(int i, int lane, int &row, int &byte) {
     if constexpr (!TR) {
         row = 8 * i + (lane >> 3);
         byte = ((lane ^ (row >> 1)) & 7) * 16;
@@ -76,6 +71,17 @@ __device__ __forceinline__ void pp_source(int i, int lane, int &row, int &byte) 
         byte = tr_swz(tr_sw(row), at % P);
         if constexpr (2 * N != P) byte = byte < 2 * N ? byte : 0;
     }
+}
+
+// Bytes by which a lane of wave load i steps back where a unit holds one step:
+// a reduction that ends in half a unit has nothing to load for the second
+// (past the last block that is past the tensor, and a buffer's range check does
+// not see the scalar offset), so those lanes load the first step's bytes again,
+// which nothing multiplies.  pitch: bytes between the source rows.
+template <int N, bool TR>
+__host__ __device__ constexpr uint32_t pp_back(int i, int lane, uint32_t pitch) {
+    if constexpr (!TR) return (uint32_t)(((lane >> 2) ^ i) & 1) * 64u;   // bit 2 of the lane's chunk
+    else return 2 * i >= PPSide<N, TR>::kInstr ? (uint32_t)kStageK * pitch : 0u;
 }
 
 // LDS byte (within the side) of the lane's fragment s of a wave whose rows or

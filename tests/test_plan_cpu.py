@@ -1,5 +1,6 @@
-"""Host-side plans of the large passes (csrc/pp_plan.h), built host-only into a
-small library: no GPU and no device code."""
+"""Host-side plans of the large passes (csrc/pp_plan.h) and the offsets of their
+loads (csrc/pp_core.h), built host-only into a small library: no GPU and no
+device code."""
 import ctypes
 import os
 import subprocess
@@ -22,6 +23,7 @@ def plan(tmp_path_factory):
     so = ctypes.CDLL(lib)
     i64, ci = ctypes.c_int64, ctypes.c_int
     so.pp_pays.argtypes = [ci, i64, i64, i64, i64, ci, ci, ci]
+    so.pp_outside.argtypes = [ci, ci, i64, i64, ci, ctypes.POINTER(ci)]
     return so
 
 
@@ -47,3 +49,18 @@ def test_large_tiles_refuse_offsets_past_32_bits(plan, variant, dx):
     # below both bounds: the pass without an output transpose is taken at n_dyad 8
     plain = OT if dx else IT
     assert plan.pp_pays(plain, 32768, 65536, 8, 4096, dx, 0, 0)
+
+
+@pytest.mark.parametrize("n", (64, 128, 192, 256))
+@pytest.mark.parametrize("tr", (0, 1))
+@pytest.mark.parametrize("bk", (32, 64, 96, 160, 288, 512))
+def test_unit_loads_stay_inside_the_block(plan, n, tr, bk):
+    """A reduction block of an odd number of 32-index steps ends in half a unit: without the step
+    back its second half would read past the block (for the last block, past the tensor)."""
+    moved = ctypes.c_int()
+    units = (bk // 32 + 1) // 2
+    for k in range(units):
+        assert plan.pp_outside(n, tr, bk, k, 1, ctypes.byref(moved)) == 0
+        assert moved.value == 0                 # the step that is multiplied keeps its bytes
+    past = plan.pp_outside(n, tr, bk, units - 1, 0, ctypes.byref(moved))
+    assert (past > 0) == (bk % 64 == 32)
