@@ -48,6 +48,7 @@ bool out_transposed(int v) { return v == DYAD_OT || v == DYAD_DT; }
 int launch_status(hipError_t e) { return e == hipSuccess ? DYAD_OK : DYAD_ERR_LAUNCH; }
 
 int run_gemm(const GemmPass &p, hipStream_t s) {
+    const dyad::WorkspaceHold hold;
     hipError_t e = dyad::skinny_ok(p) ? dyad::launch_skinny_gemm(p, s) : hipErrorNotSupported;
     if (e == hipErrorNotSupported) e = dyad::launch_mfma_gemm(p, s);
     if (e == hipErrorNotSupported) e = dyad::launch_padded_gemm(p, s);
@@ -92,6 +93,7 @@ static int forward_impl(int variant, int64_t n_in, int64_t n_out, int64_t n_dyad
     if (act_in == DYAD_ACT_GELU) {
         // only the matrix-core tiles apply an input activation; other shapes are refused
         p.gelu_in = true;
+        const dyad::WorkspaceHold hold;
         const hipError_t e = dyad::launch_mfma_gemm(p, stream);
         return e == hipErrorNotSupported ? DYAD_ERR_SHAPE : launch_status(e);
     }

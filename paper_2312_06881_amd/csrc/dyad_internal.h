@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 namespace dyad {
 
 enum Dtype { kF32 = 0, kBF16 = 1 };
@@ -101,6 +103,32 @@ hipError_t launch_skinny_gemm(const GemmPass &p, hipStream_t s);
 // perm_last, the last slice holds block-order sums: output column j*D + g at
 // column g*bn + j).
 hipError_t split_workspace(hipStream_t s, size_t bytes, void **out);
+
+// Lives on the calling thread over all launches of a pass: split_workspace
+// leaves the lock of the buffer it hands out here, so that no other thread's
+// pass on the stream enqueues between two launches that pass data in it.
+class WorkspaceHold {
+public:
+    WorkspaceHold() : prev_(t_current) { t_current = this; }
+    ~WorkspaceHold() {
+        if (mu_) mu_->unlock();
+        t_current = prev_;
+    }
+    WorkspaceHold(const WorkspaceHold &) = delete;
+    WorkspaceHold &operator=(const WorkspaceHold &) = delete;
+    static WorkspaceHold *current() { return t_current; }
+    void take(std::mutex &mu) {
+        if (mu_ == &mu) return;   // a pass that asks again
+        if (mu_) mu_->unlock();
+        mu_ = &mu;
+        mu.lock();
+    }
+
+private:
+    static inline thread_local WorkspaceHold *t_current = nullptr;
+    WorkspaceHold *prev_;
+    std::mutex *mu_ = nullptr;
+};
 
 // dyad_forward_noalloc: while a ScratchScope lives on the calling thread,
 // split_workspace hands out its fixed buffer instead of the stream's pool

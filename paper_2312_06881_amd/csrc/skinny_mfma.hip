@@ -27,9 +27,6 @@
 // their rows further and add their accumulators through LDS in wave order
 // before storing the partial sums; above 32 tokens they split the batch
 // instead, 32 tokens a wave, each looping over chunks of the reduction.
-#include <mutex>
-#include <vector>
-
 #include "dyad_internal.h"
 #include "mfma_common.h"
 
@@ -405,87 +402,7 @@ hipError_t launch_part_mt(const SkArgs &a, int kr, bool w_t, bool g2, hipStream_
     return g2 ? launch_part_kr<MT, false, true>(a, kr, s) : launch_part_kr<MT, false, false>(a, kr, s);
 }
 
-// Partial-sum workspace: one buffer per (device, stream), from a
-// stream-ordered pool per device, kept between calls and regrown in stream
-// order (the old buffer is freed on the same stream), so calls on one stream
-// reuse it in order and calls on different streams never share it.
-struct StreamWorkspace {
-    int dev;
-    hipStream_t stream;
-    void *ptr;
-    size_t bytes;
-};
-std::mutex g_ws_mu;
-hipMemPool_t g_pool[64] = {};
-std::vector<StreamWorkspace> g_ws;
-
-hipError_t pool_of(int dev, hipMemPool_t *out) {
-    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    if (!g_pool[dev]) {
-        hipMemPoolProps props = {};
-        props.allocType = hipMemAllocationTypePinned;
-        props.handleTypes = hipMemHandleTypeNone;
-        props.location.type = hipMemLocationTypeDevice;
-        props.location.id = dev;
-        hipMemPool_t pool = nullptr;
-        hipError_t e = hipMemPoolCreate(&pool, &props);
-        if (e != hipSuccess) return e;
-        uint64_t keep = UINT64_MAX;   // keep freed blocks in the pool
-        e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-        if (e != hipSuccess) {
-            (void)hipMemPoolDestroy(pool);
-            return e;
-        }
-        g_pool[dev] = pool;
-    }
-    *out = g_pool[dev];
-    return hipSuccess;
-}
-
 }  // namespace
-
-hipError_t split_workspace(hipStream_t s, size_t bytes, void **out) {
-    if (const ScratchScope *sc = current_scratch()) {
-        // the fixed scratch of dyad_forward_noalloc: never grown, never allocated
-        if (bytes > sc->bytes) return hipErrorOutOfMemory;
-        *out = sc->ptr;
-        return hipSuccess;
-    }
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(g_ws_mu);
-    StreamWorkspace *w = nullptr;
-    for (auto &x : g_ws)
-        if (x.dev == dev && x.stream == s) w = &x;
-    if (w && w->bytes >= bytes) {
-        *out = w->ptr;
-        return hipSuccess;
-    }
-    // No allocation (or regrowth) while the stream is being captured into a
-    // graph: the buffer would belong to the graph, not to later eager calls.
-    // The caller then takes a plan that needs no buffer.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    e = hipStreamIsCapturing(s, &cap);
-    if (e != hipSuccess) return e;
-    if (cap != hipStreamCaptureStatusNone) return hipErrorNotSupported;
-    hipMemPool_t pool;
-    e = pool_of(dev, &pool);
-    if (e != hipSuccess) return e;
-    const size_t want = bytes < ((size_t)1 << 20) ? ((size_t)1 << 20) : bytes;
-    void *p = nullptr;
-    e = hipMallocFromPoolAsync(&p, want, pool, s);
-    if (e != hipSuccess) return e;
-    if (w) {
-        (void)hipFreeAsync(w->ptr, s);
-        w->ptr = p;
-        w->bytes = want;
-    } else {
-        g_ws.push_back(StreamWorkspace{dev, s, p, want});
-    }
-    *out = p;
-    return hipSuccess;
-}
 
 hipError_t launch_split_reduce(const GemmPass &p, const float *part, int slices, hipStream_t s, bool perm_last,
                                int perm_from) {

@@ -4,7 +4,9 @@
   width included, checked against the dense weight its own forward pass spans;
 * the C-ABI layer (argument checks, pass descriptions, workspace checks) built
   host-only with mock kernel launchers, including a launcher that fails, which
-  must come back as DYAD_ERR_LAUNCH.
+  must come back as DYAD_ERR_LAUNCH;
+* the per-stream scratch buffer under ThreadSanitizer, with mock HIP calls: two
+  host threads on one stream, and a buffer that a captured graph refers to.
 """
 import os
 import shutil
@@ -44,3 +46,13 @@ def test_abi_layer_under_sanitizers_with_mock_launchers(tmp_path):
     _run(cmd)
     r = _run([exe], env={**os.environ, "ASAN_OPTIONS": "detect_leaks=0"})
     assert "abi mock ok" in r.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(CLANG), reason="ROCm clang not installed")
+def test_stream_buffer_under_thread_sanitizer_with_mock_hip(tmp_path):
+    exe = str(tmp_path / "workspace_mock")
+    csrc = os.path.join(ROOT, "paper_2312_06881_amd", "csrc")
+    _run([CLANG, "-x", "hip", "--offload-host-only", "-std=c++17", "-fsanitize=thread", "-g", "-O1", "-I", csrc,
+          os.path.join(csrc, "stream_workspace.hip"), os.path.join(HERE, "workspace_mock.cpp"), "-o", exe, "-pthread"])
+    r = _run([exe], env={**os.environ, "TSAN_OPTIONS": "halt_on_error=1"})
+    assert "workspace mock ok" in r.stdout
