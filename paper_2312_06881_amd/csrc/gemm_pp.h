@@ -6,6 +6,7 @@
 // A tile lies in one output block g.  FORM:
 //   kPPPair   both components in one loop, component 2 reading in2 (the
 //             de-interleaved copy, or in) at the first's places; epilogue
+//   kPPPairOne  the same for reduction blocks of one step (32 indices)
 //   kPPSlice  component 1's sums into fp32 slice a.slice0 of a.part
 //   kPPAdd    component 1, plus the slice's sums (at the block-order place of
 //             each column with a.unperm); epilogue
@@ -26,8 +27,6 @@
 #include "pp_plan.h"
 
 namespace dyad {
-
-enum PPForm { kPPPair = 0, kPPSlice = 1, kPPAdd = 3, kPPPadAdd = 4, kPPPadPair = 5, kPPRes = 6 };
 
 template <int BM, int BN, int WGM, int WGN, bool W_T>
 struct PPCfg {
@@ -285,8 +284,8 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
     using C = PPCfg<BM, BN, WGM, WGN, W_T>;
     using SA = typename C::A;
     using SB = typename C::B;
-    constexpr bool kRes = FORM == kPPRes;
-    constexpr bool kPair = FORM == kPPPair || FORM == kPPPadPair || kRes;
+    constexpr bool kRes = FORM == kPPRes, kOne = FORM == kPPPairOne;
+    constexpr bool kPair = FORM == kPPPair || FORM == kPPPadPair || kRes || kOne;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
     lds_u8 *lds = (lds_u8 *)smem;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -325,6 +324,7 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
         pp_source<BM, false>(i, lane, row, byte);
         voA[q] = (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)(g * bk) * 2u + (uint32_t)byte;
         if constexpr (kRes) voA2[q] = (uint32_t)row * (uint32_t)Kin * 2u + (uint32_t)(r * bk) * 2u + (uint32_t)byte;
+        if constexpr (kOne) voA[q] -= pp_back<BM, false>(i, lane, 0u);
         loA[q] = 1024u * (uint32_t)i;
     }
 #pragma unroll
@@ -343,45 +343,34 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
             }
         } else if constexpr (W_T) voB[q] = ((uint32_t)(g * bk + row) * (uint32_t)bn + (uint32_t)jb) * 2u + (uint32_t)byte;
         else voB[q] = (uint32_t)(g * bn + jb + row) * (uint32_t)bk * 2u + (uint32_t)byte;
+        if constexpr (kOne) voB[q] -= pp_back<BN, W_T>(i, lane, (uint32_t)bn * 2u);
         loB[q] = (uint32_t)C::kOffB + 1024u * (uint32_t)i;
     }
-    // steps back of a one-step unit; a side's loads alternate waves, so without
-    // W_T one value serves all of them
-    const uint32_t backA = pp_back<BM, false>(wave, lane, 0u);
-    uint32_t backB[SB::kPer];
-#pragma unroll
-    for (int q = 0; q < SB::kPer; ++q) backB[q] = pp_back<BN, W_T>(W_T ? pp_instr(wave, q) : wave, lane, (uint32_t)bn * 2u);
-    const uint32_t stepB = W_T ? (uint32_t)(kPPK * 2) * (uint32_t)bn : (uint32_t)(kPPK * 2);
-    const int nk = (ks + 1) / 2;                   // units per component; the last may hold one step
+    const uint32_t stepB = W_T ? (uint32_t)(kStageK * 2) * (uint32_t)bn : (uint32_t)(kStageK * 2);
+    const int nk = (ks + 1) / 2;                   // units per component; the last may hold one new step
     const int units = kPair ? 2 * nk : nk;
     // unit d: components alternate in the paired forms
-    auto unit_k = [&](int d) {
-        const int k = kPair ? d >> 1 : d;
-        return (uint32_t)(k < nk ? k : nk - 1);
-    };
-    auto both = [&](int d) { return 2 * (int)unit_k(d) + 1 < ks; };
+    auto unit_k = [&](int d) { return kPair ? d >> 1 : d; };
+    auto both = [&](int d) { return 2 * unit_k(d) + 1 < ks; };
+    auto unit_step = [&](int d) { return (uint32_t)(kOne ? 0 : pp_unit_step(unit_k(d), ks)); };
     auto issue_a = [&](int d) {
         const __amdgpu_buffer_rsrc_t rs = kPair && (d & 1) ? rA2 : rA1;
         lds_u8 *slot = lds + d % C::kSlotA * SA::kBytes;
-        const bool one = !both(d);
 #pragma unroll
         for (int q = 0; q < SA::kPer; ++q) {
             uint32_t vo = voA[q];
             if constexpr (kRes) vo = d & 1 ? voA2[q] : vo;
-            vo -= one ? backA : 0u;
-            dma16(rs, slot + loA[q], vo, unit_k(d) * (uint32_t)(kPPK * 2));
+            dma16(rs, slot + loA[q], vo, unit_step(d) * (uint32_t)(kStageK * 2));
         }
     };
     auto issue_b = [&](int d) {
         const __amdgpu_buffer_rsrc_t rs = kPair && (d & 1) ? rW2 : rW1;
         lds_u8 *slot = lds + d % C::kSlotB * SB::kBytes;
-        const bool one = !both(d);
 #pragma unroll
         for (int q = 0; q < SB::kPer; ++q) {
             uint32_t vo = voB[q];
             if constexpr (kRes) vo = d & 1 ? voB2[q] : vo;
-            vo -= one ? backB[q] : 0u;
-            dma16(rs, slot + loB[q], vo, unit_k(d) * stepB);
+            dma16(rs, slot + loB[q], vo, unit_step(d) * stepB);
         }
     };
     const int wm0 = (wave / WGN) * C::WM, wn0 = (wave % WGN) * C::WN;
@@ -416,6 +405,7 @@ hipError_t launch_pp_tile(GemmArgs a, hipStream_t s) {
     const int64_t tiles_m = (a.M + BM - 1) / BM, tiles_n = a.Nout / BN;
     if (!pp_fits(BM, a.Kin, a.Nout, a.D * a.bn * a.bk) || tiles_m * tiles_n >= ((int64_t)1 << 31))
         return hipErrorNotSupported;
+    if ((a.bk < kPPK) != (FORM == kPPPairOne)) return hipErrorNotSupported;
     if (FORM == kPPRes && (a.bn % a.D != 0 || a.bn / a.D % BN != 0)) return hipErrorNotSupported;
     a.tiles_n = (int)tiles_n;
     a.tiles_total = (int)(tiles_m * tiles_n);

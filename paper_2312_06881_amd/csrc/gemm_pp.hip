@@ -32,7 +32,12 @@ hipError_t launch_form(const GemmArgs &a, hipStream_t s) {
 template <bool W_T>
 hipError_t launch_w(int form, const GemmArgs &a, hipStream_t s) {
     switch (form) {
-    case kPPPair: return launch_form<W_T, kPPPair>(a, s);
+    case kPPPair:
+        // one step a component: epilogues all but alone, two workgroups a CU
+        if (a.bk < kPPK)
+            return a.bn % 128 == 0 ? launch_pp_tile<128, 128, 2, 4, W_T, kPPPairOne>(a, s)
+                                   : launch_pp_tile<128, 64, 4, 2, W_T, kPPPairOne>(a, s);
+        return launch_form<W_T, kPPPair>(a, s);
     case kPPSlice: return launch_form<W_T, kPPSlice>(a, s);
     case kPPAdd: return launch_form<W_T, kPPAdd>(a, s);
     case kPPPadAdd: return launch_form<W_T, kPPPadAdd>(a, s);

@@ -24,7 +24,8 @@ template <bool W_T>
 hipError_t launch_padded_as(const GemmPass &p, hipStream_t s) {
     const int64_t D = p.D, bk = p.bk, bn = p.bn;
     // (room for the zero columns in front of a block: see pp_epilogue)
-    const int64_t bkp = pad_up(bk, kStageK), bnp = pad_up(bn % 8 == 0 ? bn : bn + 7, 64);
+    const int64_t bkp = bk <= kPPK ? kPPK : pad_up(bk, kStageK);   // (at least one unit)
+    const int64_t bnp = pad_up(bn % 8 == 0 ? bn : bn + 7, 64);
     const int64_t Kp = D * bkp, Np = D * bnp;
     // 32-bit offsets: one tile's rows of the copies, slice and output
     if ((int64_t)256 * Np * 4 >= ((int64_t)1 << 31) || (int64_t)256 * Kp * 2 >= ((int64_t)1 << 31) ||

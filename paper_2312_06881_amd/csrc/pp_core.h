@@ -73,11 +73,16 @@ __host__ __device__ __forceinline__ void pp_source(int i, int lane, int &row, in
     }
 }
 
-// Bytes by which a lane of wave load i steps back where a unit holds one step:
-// a reduction that ends in half a unit has nothing to load for the second
-// (past the last block that is past the tensor, and a buffer's range check does
-// not see the scalar offset), so those lanes load the first step's bytes again,
-// which nothing multiplies.  pitch: bytes between the source rows.
+// First of the two steps that unit k of a reduction of ks >= 2 steps loads.
+// Where ks is odd the last unit holds one new step, its second, behind the step
+// before: a unit that began at its only step would load past the block (past the
+// tensor for the last one, and a buffer's range check does not see the scalar
+// offset).  Units past the last load it again.
+__host__ __device__ constexpr int pp_unit_step(int k, int ks) { return 2 * k < ks - 2 ? 2 * k : ks - 2; }
+
+// A reduction of one step has no step before it: the lanes of the second half
+// step back by these bytes and load the first's again (pitch: bytes between the
+// source rows).  The step to multiply is the second here too.
 template <int N, bool TR>
 __host__ __device__ constexpr uint32_t pp_back(int i, int lane, uint32_t pitch) {
     if constexpr (!TR) return (uint32_t)(((lane >> 2) ^ i) & 1) * 64u;   // bit 2 of the lane's chunk
@@ -212,7 +217,8 @@ __device__ __forceinline__ void pp_read(const uint32_t (&pa)[TA ? SM : 1], const
 // the wave's NVA / NVB loads of unit d's sides into slots d % SLOTA and
 // d % SLOTB (for d >= units they load a valid unit again: its slot is never
 // read); addr(d, h, pa, pb) gives the fragment addresses of step h;
-// both(d) says whether unit d has a second step.  LDS is free, and no load is
+// both(d) says whether unit d has two steps to multiply, or the second alone.
+// LDS is free, and no load is
 // in flight, when it returns (after a barrier).
 // Side B's fragments are the first MFMA operand, so a lane's four sums lie
 // along side B (4 (l / 16) + v) at row l % 16 of side A.
@@ -249,14 +255,14 @@ __device__ __forceinline__ void pp_loop(int units, int wave, f32x4_t (&acc)[SM][
         addr(d, 0, pa, pb);
         pp_read<SM, SN, TA, TB, SA, SB>(pa, pb, a, b);
         pp_barrier();
-        multiply();
+        if (both(d)) multiply();
         pp_barrier();
         issue_a(d + SLOTA - 1);
         addr(d, 1, pa, pb);
         pp_read<SM, SN, TA, TB, SA, SB>(pa, pb, a, b);
         if (half) wait_vm<kLeft>();
         pp_barrier();
-        if (both(d)) multiply();
+        multiply();
         if (!half) wait_vm<kLeft>();
         pp_barrier();
     }

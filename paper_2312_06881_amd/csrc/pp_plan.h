@@ -6,6 +6,9 @@
 
 namespace dyad {
 
+// Forms of a launch of the large tiles (gemm_pp.h).
+enum PPForm { kPPNone = 0, kPPPair = 1, kPPSlice = 2, kPPAdd = 3, kPPPadAdd = 4, kPPPadPair = 5, kPPRes = 6, kPPPairOne = 7 };
+
 // Whether the 32-bit byte offsets of a tile of BM token rows reach all of it:
 // its input and output panels (fp32 sums included) and one weight tensor of
 // `weights` entries.  The tiles of the other matrix-core kernels have the same

@@ -29,29 +29,36 @@ int pp_pays(int variant, int64_t n_in, int64_t n_out, int64_t D, int64_t M, int 
 }
 
 // Loads of one unit k of a side (N rows of 2 * bk bytes, or with tr bk rows of N
-// columns): how many lanes read outside those bytes, stepping back in a unit of
-// one step or (back == 0) not, and how many first-step lanes step back at all.
-int pp_outside(int n, int tr, int64_t bk, int64_t k, int back, int *moved) {
+// columns).  Returns how many lanes read outside those bytes, with the unit
+// starting at pp_unit_step (or stepping back in a reduction of one step), or with
+// plain != 0 at step 2 k.  wrong: lanes of a step that is multiplied whose bytes
+// are not that step's.
+int pp_outside(int n, int tr, int64_t bk, int64_t k, int plain, int *wrong) {
     int bad = 0;
-    *moved = 0;
+    *wrong = 0;
     auto side = [&](auto N, auto TR) {
         constexpr int kN = decltype(N)::value;
         constexpr bool kTR = decltype(TR)::value;
         using S = dyad::PPSide<kN, kTR>;
-        const int64_t pitch = kTR ? 2 * kN : 2 * bk, ks = bk / dyad::kStageK;
-        const bool one = 2 * k + 1 >= ks;
+        const int64_t pitch = kTR ? 2 * kN : 2 * bk, step = kTR ? dyad::kStageK * pitch : 2 * dyad::kStageK;
+        const int ks = (int)(bk / dyad::kStageK);
+        const bool one = ks == 1, both = 2 * k + 1 < ks;
+        const int64_t start = (plain ? 2 * k : one ? 0 : dyad::pp_unit_step((int)k, ks)) * step;
         for (int wave = 0; wave < dyad::kPPWaves; ++wave)
             for (int q = 0; q < S::kPer; ++q)
                 for (int lane = 0; lane < 64; ++lane) {
                     int row, byte;
                     const int i = dyad::pp_instr(wave, q);
                     dyad::pp_source<kN, kTR>(i, lane, row, byte);
-                    const int64_t step = one && back ? dyad::pp_back<kN, kTR>(i, lane, (uint32_t)pitch) : 0;
-                    const bool first = kTR ? row < dyad::kStageK : byte < 2 * dyad::kStageK;
-                    *moved += first && step != 0;
-                    const int64_t at = row * pitch + byte - step + k * (kTR ? dyad::kPPK * pitch : 2 * dyad::kPPK);
+                    const int64_t back = one && !plain ? dyad::pp_back<kN, kTR>(i, lane, (uint32_t)pitch) : 0;
+                    const int64_t at = row * pitch + byte - back + start;
                     const int64_t lo = kTR ? 0 : row * pitch, hi = kTR ? bk * pitch : lo + 2 * bk;
                     bad += at < lo || at + 16 > hi;
+                    // the loop multiplies both steps, or the second alone: step 2 k + h, or the last
+                    const int h = kTR ? row / dyad::kStageK : byte / (2 * dyad::kStageK);
+                    if (!both && h == 0) continue;
+                    const int64_t want = both ? 2 * k + h : ks - 1;
+                    *wrong += (kTR ? at / pitch / dyad::kStageK : (at - lo) / (2 * dyad::kStageK)) != want;
                 }
     };
     auto with = [&](auto TR) {

@@ -55,12 +55,12 @@ def test_large_tiles_refuse_offsets_past_32_bits(plan, variant, dx):
 @pytest.mark.parametrize("tr", (0, 1))
 @pytest.mark.parametrize("bk", (32, 64, 96, 160, 288, 512))
 def test_unit_loads_stay_inside_the_block(plan, n, tr, bk):
-    """A reduction block of an odd number of 32-index steps ends in half a unit: without the step
-    back its second half would read past the block (for the last block, past the tensor)."""
-    moved = ctypes.c_int()
+    """A reduction block of an odd number of 32-index steps ends in a unit of one new step: started
+    at that step, its second half would read past the block (for the last block, past the tensor)."""
+    wrong = ctypes.c_int()
     units = (bk // 32 + 1) // 2
     for k in range(units):
-        assert plan.pp_outside(n, tr, bk, k, 1, ctypes.byref(moved)) == 0
-        assert moved.value == 0                 # the step that is multiplied keeps its bytes
-    past = plan.pp_outside(n, tr, bk, units - 1, 0, ctypes.byref(moved))
+        assert plan.pp_outside(n, tr, bk, k, 0, ctypes.byref(wrong)) == 0
+        assert wrong.value == 0                 # every step is multiplied once, from its own bytes
+    past = plan.pp_outside(n, tr, bk, units - 1, 1, ctypes.byref(wrong))
     assert (past > 0) == (bk % 64 == 32)
