@@ -13,19 +13,33 @@ namespace {
 // slices staged through LDS (768 -> 3072, n_dyad 5, 8192 tokens, GELU forward:
 // pair 92 -> 83 us, slice 171 -> 143; 3072 -> 768 at 640 a block 76 -> 72 the
 // other way; 8192 -> 32768, n_dyad 16, 4096 tokens, 512 a block 495 -> 529).
+//   - Padded blocks that add a slice take no tile above 128 x 128 that divides
+//     them: the larger ones hold more than a wave's registers (768 -> 3072,
+//     n_dyad 12: 0.65-0.75x of the fused-stage tiles, 128 x 128 1.17x).
+//   - 192-wide tiles that fill only part of the GPU beat 64-wide ones in more
+//     than one round (1536 -> 6144, n_dyad 8, 3328 tokens, input gradient 0.75x
+//     -> 1.02x of the earlier tiles).
+//   - Of the 64-wide tiles the tall one pays only with untransposed weights and
+//     no slice to add (padded 2048 -> 2048, n_dyad 3, input gradient 0.88 -> 1.0x).
 template <bool W_T, int FORM>
 hipError_t launch_form(const GemmArgs &a, hipStream_t s) {
     const int64_t tm = (a.M + 255) / 256;
     const int64_t w = FORM == kPPRes && a.bn % a.D == 0 ? a.bn / a.D : a.bn;
-    const bool add = FORM == kPPAdd || FORM == kPPPadAdd;
+    constexpr bool add = FORM == kPPAdd || FORM == kPPPadAdd;
     auto fills = [&](int bn) { return tm * (a.Nout / bn) >= 192; };
-    if (w % 256 == 0 && fills(256)) return launch_pp_tile<256, 256, 2, 4, W_T, FORM>(a, s);
-    if (w % 192 == 0 && fills(192)) return launch_pp_tile<256, 192, 4, 2, W_T, FORM>(a, s);
+    if constexpr (FORM == kPPPadAdd) {
+        if (w % 128 == 0) return launch_pp_tile<128, 128, 2, 4, W_T, FORM>(a, s);
+    } else {
+        if (w % 256 == 0 && fills(256)) return launch_pp_tile<256, 256, 2, 4, W_T, FORM>(a, s);
+    }
+    if (w % 192 == 0 && (fills(192) || (FORM == kPPPair && w % 128 != 0 && tm * (a.Nout / 64) > 256)))
+        return launch_pp_tile<256, 192, 4, 2, W_T, FORM>(a, s);
     if (w % 128 == 0 && (add || a.bk < 512 || !fills(128))) return launch_pp_tile<128, 128, 2, 4, W_T, FORM>(a, s);
-    if (w % 128 == 0) return launch_pp_tile<256, 128, 4, 2, W_T, FORM>(a, s);
-    if (w % 64 == 0 && ((add && W_T) || (!add && a.bk < 512) || !fills(64)))
-        return launch_pp_tile<128, 64, 4, 2, W_T, FORM>(a, s);
-    if (w % 64 == 0) return launch_pp_tile<256, 64, 4, 2, W_T, FORM>(a, s);
+    if constexpr (!add)
+        if (w % 128 == 0) return launch_pp_tile<256, 128, 4, 2, W_T, FORM>(a, s);
+    if (w % 64 == 0 && (add || W_T || a.bk < 512 || !fills(64))) return launch_pp_tile<128, 64, 4, 2, W_T, FORM>(a, s);
+    if constexpr (!add && !W_T)
+        if (w % 64 == 0) return launch_pp_tile<256, 64, 4, 2, W_T, FORM>(a, s);
     return hipErrorNotSupported;
 }
 

@@ -14,18 +14,49 @@
 // real column.  The epilogue writes real columns only (pp_epilogue, PAD).
 #pragma once
 
+#include "gemm_mfma2.h"
 #include "gemm_pp.h"
 
 namespace dyad {
+
+// ---- the fused-stage tiles, where padded_fused() prefers them -------------------
+
+template <int BM, int BN, int WGM, int WGN, bool W_T, int ONLY>
+hipError_t launch_pad_tile(const GemmArgs &a0, hipStream_t s) {
+    using C = Gemm2Cfg<BM, BN, WGM, WGN, 1, false, false, W_T>;
+    GemmArgs a = a0;
+    const int64_t tiles_m = (a.M + BM - 1) / BM;
+    const int64_t tiles_n = a.Nout / BN;
+    if (a.Nout % BN != 0 || tiles_m * tiles_n >= ((int64_t)1 << 31)) return hipErrorNotSupported;
+    a.tiles_n = (int)tiles_n;
+    a.tiles_total = (int)(tiles_m * tiles_n);
+    a.splits = 1;
+    dyad_gemm_mfma2<BM, BN, WGM, WGN, 1, false, false, W_T, ONLY><<<a.tiles_total, C::kThreads, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+// The tiles of one form: ONLY = 1 (component 2 into the slice) or 4 (component
+// 1 adding it).  Output blocks of a multiple of 256, 192, 128 or 64 columns,
+// 8-wave tiles where they fill the GPU.
+template <bool W_T, int ONLY>
+hipError_t launch_pad_form(const GemmArgs &a, hipStream_t s) {
+    const int64_t bnp = a.bn;
+    auto enough = [&](int bm, int bn_tile) { return ((a.M + bm - 1) / bm) * (a.Nout / bn_tile) >= 256; };
+    if (bnp % 256 == 0 && enough(256, 256)) return launch_pad_tile<256, 256, 2, 4, W_T, ONLY>(a, s);
+    if (bnp % 192 == 0 && enough(256, 192)) return launch_pad_tile<256, 192, 4, 2, W_T, ONLY>(a, s);
+    if (bnp % 128 == 0) return launch_pad_tile<128, 128, 2, 2, W_T, ONLY>(a, s);
+    return launch_pad_tile<128, 64, 2, 2, W_T, ONLY>(a, s);
+}
 
 // Whole pass on the padded forms (GemmPass p: real widths and blocks).
 // Token chunks keep the workspace (input copies and slice) within 2 GiB.
 template <bool W_T>
 hipError_t launch_padded_as(const GemmPass &p, hipStream_t s) {
     const int64_t D = p.D, bk = p.bk, bn = p.bn;
-    // (room for the zero columns in front of a block: see pp_epilogue)
-    const int64_t bkp = bk <= kPPK ? kPPK : pad_up(bk, kStageK);   // (at least one unit)
-    const int64_t bnp = pad_up(bn % 8 == 0 ? bn : bn + 7, 64);
+    const bool fused = padded_fused(p, pad_up(bk, kStageK));
+    const int64_t bkp = bk <= kPPK && !fused ? kPPK : pad_up(bk, kStageK);   // (at least one unit)
+    // (the large tiles want room for the zero columns in front of a block: see pp_epilogue)
+    const int64_t bnp = pad_up(bn % 8 == 0 || fused ? bn : bn + 7, 64);
     const int64_t Kp = D * bkp, Np = D * bnp;
     // 32-bit offsets: one tile's rows of the copies, slice and output
     if ((int64_t)256 * Np * 4 >= ((int64_t)1 << 31) || (int64_t)256 * Kp * 2 >= ((int64_t)1 << 31) ||
@@ -54,7 +85,7 @@ hipError_t launch_padded_as(const GemmPass &p, hipStream_t s) {
     const int64_t R = W_T ? bk : bn, Cc = W_T ? bn : bk, Rp = W_T ? bkp : bnp, Cp = W_T ? bnp : bkp;
     // outputs of the pass's epilogue are shifted; the slice's are not
     hipError_t e = launch_pad_weights(static_cast<const uint16_t *>(p.W1), static_cast<const uint16_t *>(p.W2), D, R, Cc,
-                                      Rp, Cp, w1p, w2p, !W_T, true, !p.out_t, s);
+                                      Rp, Cp, w1p, w2p, !W_T, !fused, !fused && !p.out_t, s);
     for (int64_t m0 = 0; m0 < p.M && e == hipSuccess; m0 += mc) {
         const int64_t mt = p.M - m0 < mc ? p.M - m0 : mc;
         e = launch_pad_rows(static_cast<const uint16_t *>(p.in) + m0 * p.Kin, mt, p.Kin, (int)D, bk, bkp, x1,
@@ -76,12 +107,15 @@ hipError_t launch_padded_as(const GemmPass &p, hipStream_t s) {
             GemmArgs c2 = a;
             c2.in = x2; c2.W1 = w2p; c2.part = slice; c2.unperm = 0;
             c2.bias = nullptr; c2.h_in = nullptr; c2.out = nullptr; c2.h_out = nullptr; c2.epilogue = kEpiBias;
-            e = launch_pp(kPPSlice, W_T, c2, s);
+            e = fused ? launch_pad_form<W_T, 1>(c2, s) : launch_pp(kPPSlice, W_T, c2, s);
             a.part = slice; a.unperm = 1;
-            if (e == hipSuccess) e = launch_pp(kPPPadAdd, W_T, a, s);
+            if (e == hipSuccess) e = fused ? launch_pad_form<W_T, 4>(a, s) : launch_pp(kPPPadAdd, W_T, a, s);
         } else {
             a.part = nullptr; a.unperm = 0;
-            e = launch_pp(kPPPadPair, W_T, a, s);
+            if constexpr (W_T)
+                e = fused ? launch_pad_tile<128, 64, 2, 2, W_T, 5>(a, s) : launch_pp(kPPPadPair, W_T, a, s);
+            else
+                e = launch_pp(kPPPadPair, W_T, a, s);
         }
     }
     return e;

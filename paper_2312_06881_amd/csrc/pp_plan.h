@@ -60,4 +60,24 @@ inline bool pp_pays(const GemmPass &p) {
     return !p.in_t && p.bn >= 256 && p.bk >= 1024;
 }
 
+// Whether a zero-padded form (padded_mfma.h) runs on the fused-stage tiles
+// instead of the large ones; bkp: reduction block rounded up to 32.
+//   Output transpose, short reductions: a tile is mostly epilogue, where the
+//   fused-stage tiles' staged stores beat a second pass over the slice in LDS.
+//     - blocks of a multiple of 8 columns, reductions up to 256 (768 -> 3072,
+//       n_dyad 16, 16384 tokens, forward 194 against 265 us; n_dyad 12 at blocks
+//       of 64 to 256 0.89-0.96x on the large tiles), while blocks that start
+//       anywhere win 1.1-1.2x there from reductions of 96;
+//     - blocks that only 64- or 192-column tiles divide: up to 64, and under 512
+//       where 192-column tiles fill the GPU (1024 -> 1024, n_dyad 5, 0.91-0.96x).
+//   Weights read transposed, blocks that only 64-column tiles divide, reductions
+//   from 1024: 0.91-0.98x on the large tiles.
+inline bool padded_fused(const GemmPass &p, int64_t bkp) {
+    const int64_t w = pad_up(p.bn, 64);
+    if (!p.out_t) return p.w_t && bkp >= 1024 && w % 128 != 0 && w % 192 != 0;
+    if (p.bn % 8 == 0) return bkp <= 256;
+    if (w % 128 == 0) return false;
+    return bkp <= 64 || (bkp < 512 && w % 192 == 0 && (p.M + 255) / 256 * (p.D * w / 192) >= 192);
+}
+
 }  // namespace dyad
