@@ -170,9 +170,9 @@ inline bool permuted_pays(int D, bool out_t, bool w_t, int64_t M, int64_t bk) {
     return bk >= 512;
 }
 
-// The same form on the large tiles of gemm_pp.h, in token chunks, for a pass
-// that pp_pays (pp_plan.h) admits; hipErrorNotSupported, launching nothing,
-// without a workspace.
+// The same form on the large tiles of gemm_pp.h, in token chunks, as pp_plan()
+// (pp_plan.h) lays it out; hipErrorNotSupported, launching nothing, where it
+// does not admit the pass or there is no workspace.
 hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s);
 
 // Zero-padded forms (padded_mfma.h): block-ordered copies padded to whole

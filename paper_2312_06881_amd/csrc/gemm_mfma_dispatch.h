@@ -389,10 +389,7 @@ hipError_t dispatch_tiles(const GemmPass &p, hipStream_t s) {
     if (p.bk % kStageK != 0) return hipErrorNotSupported;
     auto enough = [&](int bm, int bn_tile) { return ((p.M + bm - 1) / bm) * (p.Nout / bn_tile) >= 256; };
     if constexpr (D == 2 || D == 4 || D >= 8)
-        if (pp_pays(p)) {
-            const hipError_t e = launch_permuted_pp(p, s);
-            if (e != hipErrorNotSupported) return e;
-        }
+        if (const hipError_t e = launch_permuted_pp(p, s); e != hipErrorNotSupported) return e;
     if constexpr (D >= 8)
         if (permuted_pays((int)D, OUT_T, W_T, p.M, p.bk)) {
             const hipError_t e = launch_permuted<D, IN_T, OUT_T, W_T>(p, s);

@@ -100,51 +100,20 @@ hipError_t launch_interleave(const uint16_t *in, uint16_t *out, int64_t M, int64
     return hipGetLastError();
 }
 
-// Large batches with a transpose on plain blocks.  An input transpose first de-interleaves the input (residue
-// g's columns k*D + g become the contiguous block g).  Without an output
-// transpose both components then run in one loop (kPPPair).  With one:
-//   - where every (block, residue) pair of the output has whole tiles of
-//     columns, both components still run in one loop over residue-major
-//     columns (kPPRes), and a copy interleaves the bf16 results (4 bytes an
-//     output; a stashed pre-activation or GELU' input moves the same way);
-//   - else component 2's sums go to an fp32 slice in block order, which
-//     component 1's epilogue adds at the block-order place of each output
-//     column (8 bytes an output and a second pass, but with output blocks that
-//     narrow the outputs are few against the reduction).
-// The tokens run in chunks of whole rounds of tiles over the GPU, kept short
-// enough that what passes between the kernels stays in the 256 MB MALL
-// (Dyad-DT 8192 -> 32768, n_dyad 16, 8192 tokens, forward: 1335 us in one
-// chunk, 1138 in chunks of 160 MB).
-constexpr size_t kPPChunkBytes = (size_t)160 << 20;
-
 hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s) {
-    if (p.bk % kStageK != 0 || p.bn % 64 != 0) return hipErrorNotSupported;
+    const PPPlan pl = pp_plan(p);
+    if (!pl.form) return hipErrorNotSupported;
     const int D = (int)p.D;
-    const bool res = pp_res_columns(p);
-    const bool slices = p.out_t && !res;
-    const bool keep_h = res && p.epilogue == kEpiBiasGelu && p.h_out;
-    const bool grad = res && p.epilogue == kEpiGeluGrad;
-    const size_t per_tok = (p.in_t ? (size_t)p.Kin * 2 : 0) + (slices ? (size_t)p.Nout * sizeof(float) : 0) +
-                           (res ? (size_t)p.Nout * 2 : 0) + (keep_h || grad ? (size_t)p.Nout * 2 : 0);
-    const size_t wcopy = res && p.w_t ? (size_t)(p.D * p.bn * p.bk) * 2 : 0;
-    int64_t mc = p.M;
-    if (per_tok > 0) {
-        // rounds of 256 tiles of 256 x 256
-        const int64_t round = 256 * ((256 * 256 + p.Nout - 1) / p.Nout);
-        const int64_t fit = (int64_t)((kPPChunkBytes) / per_tok) / round * round;
-        mc = fit > round ? fit : round;
-        if (mc > p.M) mc = p.M;
-    }
-    if (per_tok * (size_t)mc + wcopy > ((size_t)2 << 30)) return hipErrorNotSupported;
+    const bool res = pl.form == kPPRes, slices = pl.form == kPPSlice;
+    const int64_t mc = pl.chunk;
     void *ws = nullptr;
-    if (per_tok + wcopy > 0 && split_workspace(s, per_tok * (size_t)mc + wcopy, &ws) != hipSuccess) {
+    if (split_workspace(s, pl.per_tok * (size_t)mc + pl.wcopy, &ws) != hipSuccess) {
         (void)hipGetLastError();
         return hipErrorNotSupported;
     }
     float *slice = static_cast<float *>(ws);
     uint16_t *yp = reinterpret_cast<uint16_t *>(slice + (slices ? mc * p.Nout : 0));
-    uint16_t *hp = yp + (res ? mc * p.Nout : 0);
-    uint16_t *xp = hp + (keep_h || grad ? mc * p.Nout : 0);
+    uint16_t *xp = yp + (res ? mc * p.Nout : 0);
     uint16_t *w1d = xp + (p.in_t ? mc * p.Kin : 0);
     GemmArgs a{};
     a.Kin = p.Kin; a.Nout = p.Nout; a.bk = p.bk; a.bn = p.bn; a.D = p.D;
@@ -153,7 +122,7 @@ hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s) {
     a.W1 = static_cast<const uint16_t *>(p.W1);
     a.W2 = static_cast<const uint16_t *>(p.W2);
     hipError_t e = hipSuccess;
-    if (wcopy) {
+    if (pl.wcopy) {
         e = launch_deinterleave(a.W1, w1d, p.D * p.bk, p.bn / p.D, D, s);
         a.W1 = w1d;
     }
@@ -162,20 +131,18 @@ hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s) {
         a.in = static_cast<const uint16_t *>(p.in) + m0 * p.Kin;
         a.in2 = a.in;
         uint16_t *out = static_cast<uint16_t *>(p.out) + m0 * p.Nout;
-        uint16_t *h_out = p.h_out ? static_cast<uint16_t *>(p.h_out) + m0 * p.Nout : nullptr;
-        const uint16_t *h_in = p.h_in ? static_cast<const uint16_t *>(p.h_in) + m0 * p.Nout : nullptr;
+        a.out = out;
+        a.h_out = p.h_out ? static_cast<uint16_t *>(p.h_out) + m0 * p.Nout : nullptr;
+        a.h_in = p.h_in ? static_cast<const uint16_t *>(p.h_in) + m0 * p.Nout : nullptr;
         if (p.in_t) {
             e = launch_deinterleave(a.in, xp, a.M, p.bk, D, s);
             a.in2 = xp;
         }
         if (res) {
-            if (e == hipSuccess && grad) e = launch_deinterleave(h_in, hp, a.M, p.Nout / D, D, s);
-            a.out = yp; a.h_out = keep_h ? hp : nullptr; a.h_in = grad ? hp : nullptr;
+            a.out = yp;
             if (e == hipSuccess) e = launch_pp(kPPRes, p.w_t, a, s);
             if (e == hipSuccess) e = launch_interleave(yp, out, a.M, p.Nout / D, D, s);
-            if (e == hipSuccess && keep_h) e = launch_interleave(hp, h_out, a.M, p.Nout / D, D, s);
-        } else if (!p.out_t) {
-            a.out = out; a.h_out = h_out; a.h_in = h_in;
+        } else if (!slices) {
             if (e == hipSuccess) e = launch_pp(kPPPair, p.w_t, a, s);
         } else {
             GemmArgs c2 = a;
@@ -183,7 +150,6 @@ hipError_t launch_permuted_pp(const GemmPass &p, hipStream_t s) {
             c2.bias = nullptr; c2.h_in = nullptr; c2.out = nullptr; c2.h_out = nullptr; c2.epilogue = kEpiBias;
             c2.part = slice; c2.unperm = 0;
             if (e == hipSuccess) e = launch_pp(kPPSlice, p.w_t, c2, s);
-            a.out = out; a.h_out = h_out; a.h_in = h_in;
             a.part = slice; a.unperm = 1;
             if (e == hipSuccess) e = launch_pp(kPPAdd, p.w_t, a, s);
         }
