@@ -4,6 +4,7 @@
 #include "gemm_mfma.h"
 #include "gemm_mfma2.h"
 #include "pp_plan.h"
+#include "tile_plan.h"
 
 namespace dyad {
 
@@ -15,25 +16,6 @@ template <class C>
 constexpr int occupancy() {
     const int acc_per_lane = C::WM * C::WN / 64;
     return (C::kThreads <= 256 && (160 * 1024) / C::kLds >= 2 && acc_per_lane <= 128) ? 2 : 1;
-}
-
-// Splits of the reduction for a launch of `tiles` output tiles: none when the
-// tiles alone fill the GPU; otherwise the fewest that give about 384 work
-// items, each split keeping at least `min_stages` stages per component, and no
-// more than keep the fp32 partial sums (written and read once) within the
-// bytes of the two weight tensors.
-inline int gemm_splits(const GemmPass &p, int64_t tiles, int min_stages) {
-    if (tiles >= 192) return 1;
-    const int ks = (int)(p.bk / kStageK);
-    const int64_t wbytes = 4 * p.D * p.bn * p.bk;
-    int best = 1;
-    for (int sp = 2; sp * min_stages <= ks; ++sp) {
-        if (ks % sp != 0) continue;
-        if ((int64_t)sp * p.M * p.Nout * 8 > wbytes) break;
-        best = sp;
-        if (tiles * sp >= 384) break;
-    }
-    return best;
 }
 
 // Workspace for `splits` partial sums of pass p on stream s; false (and no
@@ -340,49 +322,32 @@ hipError_t launch_permuted(const GemmPass &p, hipStream_t s) {
     }
 }
 
-// The 4-wave tile and reduction splits of a pass, largest tile first:
-//   - a tile that gives the GPU 256 workgroups by itself (384 where the
-//     reduction is short, under 12 stages a component, and the epilogue wants a
-//     second workgroup on the CU to hide behind; 128 at n_dyad 8 and 16 with an
-//     input transpose, where every column tile reads whole spans of the input);
-//   - untransposed weights: 64 x 64 alone from 192, then the largest tile that
-//     reaches 192 with up to 4 splits of at least 4 stages;
-//   - weights read transposed: the largest tile that reaches 144 alone or 192
-//     with up to 4 splits (narrow tiles leave most threads without a weight
-//     block to transpose), then 64 x 64 alone;
-//   - else 64 x 64 with up to 8 splits.
-// Measured on gfx950 over 1 to 4096 tokens against the largest tile that
-// fits, which left up to 7/8 of the CUs idle: OPT-125m fc2 forward 42 -> 12 us
-// at 256 tokens, 41 -> 24 at 2047 (64 x 64), 42 -> 31 at 4096 (64 x 192); fc1
-// input gradient of Dyad-IT 44 -> 26 at 2047 (128 x 192, 4 splits); 8192 ->
-// 2048, n_dyad 4, 512 tokens 47 -> 32 (128 x 128, 4 splits).
-struct TileChoice {
-    int bm = 0, bn = 0, splits = 1;
-    int rank = 0;
+// The 4-wave tiles of a pass, largest first (an output transpose's D slabs let
+// only 64 x 256 run twice per CU; n_dyad 8 and 16 keep 64 tokens for the same
+// reason).
+template <int D, bool OUT_T, class F>
+void each_tile(F f) {
+    constexpr bool low = D < 8;
+    auto one = [&](auto bm, auto bn) {
+        if constexpr (tile_ok<decltype(bm)::value, decltype(bn)::value, 2, 2, D, OUT_T>()) f(bm, bn);
+    };
+    if constexpr (low && !OUT_T) one(std::integral_constant<int, 128>{}, std::integral_constant<int, 256>{});
+    if constexpr ((!low || OUT_T) && D < 16) one(std::integral_constant<int, 64>{}, std::integral_constant<int, 256>{});
+    if constexpr (low) one(std::integral_constant<int, 128>{}, std::integral_constant<int, 192>{});
+    if constexpr (low) one(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{});
+    if constexpr (low) one(std::integral_constant<int, 128>{}, std::integral_constant<int, 64>{});
+    one(std::integral_constant<int, 64>{}, std::integral_constant<int, 192>{});
+    one(std::integral_constant<int, 64>{}, std::integral_constant<int, 128>{});
+    one(std::integral_constant<int, 64>{}, std::integral_constant<int, 64>{});
+}
 
-    void consider(const GemmPass &p, int tm, int tn) {
-        if (p.bn % tn != 0) return;
-        const int64_t tiles = (p.M + tm - 1) / tm * (p.Nout / tn);
-        const int ks = (int)(p.bk / kStageK);
-        const bool smallest = tm == 64 && tn == 64;
-        const int enough = p.D >= 8 && p.in_t ? 128 : ks < 12 ? 384 : p.w_t ? 144 : 256;
-        int r = 1, sp = 1;
-        if (tiles >= enough && !(smallest && p.w_t)) {
-            r = 4;
-        } else if (smallest && tiles >= 192) {
-            r = p.w_t ? 2 : 3;
-        } else {
-            for (int k = 2; k <= 8 && tiles * sp < 192; ++k)
-                if (ks % k == 0 && ks / k >= 4 && (int64_t)k * p.M * p.Nout * 4 <= ((int64_t)64 << 20)) sp = k;
-            if (tiles * sp >= 192 && sp <= 4) r = p.w_t ? 4 : 2;
-        }
-        // ties go to the earlier, larger tile, except that the smallest is
-        // taken where none reaches 192 workgroups
-        if (r > rank || (r == 1 && rank == 1)) {
-            bm = tm; bn = tn; splits = sp; rank = r;
-        }
-    }
-};
+template <int D, bool OUT_T>
+TileChoice choose_tile(const GemmPass &p) {
+    TileChoice t;
+    each_tile<D, OUT_T>([&](auto bm, auto bn) { t.consider(p, bm, bn); });
+    t.settle(p);
+    return t;
+}
 
 template <int D, bool IN_T, bool OUT_T, bool W_T>
 hipError_t dispatch_tiles(const GemmPass &p, hipStream_t s) {
@@ -469,27 +434,11 @@ hipError_t dispatch_tiles(const GemmPass &p, hipStream_t s) {
             const hipError_t e = launch_components<D, IN_T, OUT_T, W_T>(p, s);
             if (e != hipErrorNotSupported) return e;
         }
-    // 4-wave tiles, largest first (an output transpose's D slabs let only
-    // 64 x 256 run twice per CU; n_dyad 8 and 16 keep 64 tokens for the same reason)
-    TileChoice t;
-    const auto each = [&](auto try_tile) {
-        constexpr bool low = D < 8;
-        if constexpr (low && !OUT_T) try_tile(std::integral_constant<int, 128>{}, std::integral_constant<int, 256>{});
-        if constexpr ((!low || OUT_T) && D < 16) try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 256>{});
-        if constexpr (low) try_tile(std::integral_constant<int, 128>{}, std::integral_constant<int, 192>{});
-        if constexpr (low) try_tile(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{});
-        try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 192>{});
-        try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 128>{});
-        try_tile(std::integral_constant<int, 64>{}, std::integral_constant<int, 64>{});
-    };
-    each([&](auto bm, auto bn) {
-        if constexpr (tile_ok<decltype(bm)::value, decltype(bn)::value, 2, 2, D, OUT_T>()) t.consider(p, bm, bn);
-    });
+    const TileChoice t = choose_tile<D, OUT_T>(p);
     hipError_t e4 = hipErrorNotSupported;
-    each([&](auto bm, auto bn) {
-        if constexpr (tile_ok<decltype(bm)::value, decltype(bn)::value, 2, 2, D, OUT_T>())
-            if (t.bm == bm && t.bn == bn)
-                e4 = launch_tile<decltype(bm)::value, decltype(bn)::value, 2, 2, D, IN_T, OUT_T, W_T>(p, s, t.splits);
+    each_tile<D, OUT_T>([&](auto bm, auto bn) {
+        if (t.bm == bm && t.bn == bn)
+            e4 = launch_tile<decltype(bm)::value, decltype(bn)::value, 2, 2, D, IN_T, OUT_T, W_T>(p, s, t.splits);
     });
     if (t.bm > 0) return e4;
     // An output transpose whose blocks are too narrow for any tile above
