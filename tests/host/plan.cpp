@@ -1,5 +1,6 @@
 // Host-side plans and load offsets of the large passes behind C names, for
 // test_plan_cpu.py.
+#include "gemm_mfma_dispatch.h"
 #include "pp_core.h"
 #include "pp_plan.h"
 
@@ -26,6 +27,38 @@ extern "C" {
 
 int pp_pays(int variant, int64_t n_in, int64_t n_out, int64_t D, int64_t M, int dx, int act, int stash) {
     return dyad::pp_pays(pass(variant, n_in, n_out, D, M, dx, act, stash));
+}
+
+// The form the pass takes (PPForm; 0: none) and its token chunk.
+int pp_plan(int variant, int64_t n_in, int64_t n_out, int64_t D, int64_t M, int dx, int act, int stash, int64_t *chunk) {
+    const dyad::PPPlan pl = dyad::pp_plan(pass(variant, n_in, n_out, D, M, dx, act, stash));
+    *chunk = pl.chunk;
+    return pl.form;
+}
+
+int padded_fused(int variant, int64_t n_in, int64_t n_out, int64_t D, int64_t M, int dx) {
+    const GemmPass p = pass(variant, n_in, n_out, D, M, dx, 0, 0);
+    return dyad::padded_fused(p, dyad::pad_up(p.bk, 32));
+}
+
+// The 4-wave tile of the pass: bm, bn, splits, and the two plans' work items.
+void tile_choice(int variant, int64_t n_in, int64_t n_out, int64_t D, int64_t M, int dx, int64_t *out) {
+    const GemmPass p = pass(variant, n_in, n_out, D, M, dx, 0, 0);
+    dyad::TileChoice t;
+    auto pick = [&](auto d) {
+        constexpr int kD = decltype(d)::value;
+        t = p.out_t ? dyad::choose_tile<kD, true>(p) : dyad::choose_tile<kD, false>(p);
+    };
+    switch (D) {
+    case 2: pick(std::integral_constant<int, 2>{}); break;
+    case 3: pick(std::integral_constant<int, 3>{}); break;
+    case 4: pick(std::integral_constant<int, 4>{}); break;
+    case 6: pick(std::integral_constant<int, 6>{}); break;
+    case 8: pick(std::integral_constant<int, 8>{}); break;
+    case 16: pick(std::integral_constant<int, 16>{}); break;
+    default: break;
+    }
+    out[0] = t.bm; out[1] = t.bn; out[2] = t.splits; out[3] = t.wide.items; out[4] = t.fill.items;
 }
 
 // Loads of one unit k of a side (N rows of 2 * bk bytes, or with tr bk rows of N

@@ -1,16 +1,18 @@
-"""GPU parity of the large-batch path for n_dyad 8 and 16 with a transpose.
+"""GPU parity of the large-batch paths for n_dyad 8 and 16 with a transpose.
 
 Forward and input gradient: input de-interleaved once, component 2 as a
 per-block GEMM into an fp32 slice, component 1 as a per-block GEMM whose
 epilogue adds that slice (read at the permuted place of each column under an
 output transpose).  They take it from 2048 tokens with reduction blocks of at
 least 256 (n_dyad 16; 128 with an output transpose, 64 for the input gradient
-under one from 8192 tokens) or 512 (n_dyad 8); the other passes of these
-shapes run on the fused tiles and are checked the same way.  Shapes cover the
-three per-block tile widths (blocks of 256, 128 and 64 columns), token counts
-that leave a ragged tile, and a wide layer whose slice does not fit the
-workspace at once, so the tokens run in chunks (checked on sampled rows, the
-chunk boundaries among them).
+under one from 8192 tokens) or 512 (n_dyad 8), unless the large plain-block tiles
+do (above 1024 tokens: passes without an output transpose, and at n_dyad 8 some
+with one; test_gpu_pp.py names their forms).  With a stashed pre-activation or
+GELU' the output-transposed passes at n_dyad 16 stay on it.  The other passes of
+these shapes run on the fused tiles and are checked the same way.  Shapes cover
+the three per-block tile widths (blocks of 256, 128 and 64 columns), token counts
+that leave a ragged tile, and a wide layer whose tokens run in chunks on either
+path (checked on sampled rows, the chunk boundaries among them).
 
 Weight gradients take it from 2048 tokens at n_dyad 16 and 8192 at n_dyad 8
 (the n_dyad 8 case here: 8200 tokens): component 2's strided operands
@@ -43,11 +45,11 @@ def case_id(c):
     return "x".join(map(str, c))
 
 
-SHAPES = [  # (n_in, n_out, n_dyad, tokens); which pass takes the path, and its tile
+SHAPES = [  # (n_in, n_out, n_dyad, tokens); the passes with long enough reductions, and their blocks
     (4096, 1024, 16, 2100),   # forward, blocks of 64
     (1024, 4096, 16, 2049),   # input gradient, blocks of 64
-    (4096, 2048, 16, 2100),   # forward (blocks of 128); input gradient of IT / DT (256)
-    (2048, 2048, 16, 2049),   # OT / DT forward, IT / DT input gradient, blocks of 128
+    (4096, 2048, 16, 2100),   # forward (blocks of 128); input gradient (256)
+    (2048, 2048, 16, 2049),   # forward and input gradient, blocks of 128
     (4096, 2048, 8, 2300),    # n_dyad 8 forward, blocks of 256
     (4096, 512, 8, 2048),     # n_dyad 8 forward, blocks of 64
     (2048, 4096, 8, 2051),    # n_dyad 8 input gradient, blocks of 256
@@ -89,28 +91,43 @@ def _draw(name, shape, std):
     return draw(name, shape, std, "bf16")
 
 
-@pytest.mark.parametrize("variant", VARIANTS)
-def test_wide_forward_chunked_sampled(variant):
-    """Wide layer 8192 -> 32768 at n_dyad 16 with 16640 tokens: the forward's
-    fp32 slice (and under an input transpose the de-interleaved input) exceeds
-    the 2 GiB workspace, so its tokens run in chunks (16384 tokens for
-    Dyad-OT, 14336 for Dyad-IT and -DT); rows on both sides of either boundary
-    are checked."""
-    n_in, n_out, D, M = 8192, 32768, 16, 16640
-    banner("permuted_wide", variant)
+WIDE = (8192, 32768, 16, 16640)
+# token chunks of the wide forward: plain on the large plain-block tiles, with the
+# pre-activations kept (output transposes) on the slice path within 2 GiB
+PLAIN_CHUNK = {"IT": 10240, "OT": 2560, "DT": 2048}
+STASH_CHUNK = {"OT": 16384, "DT": 14336}
+
+
+@pytest.mark.parametrize("case", [(v, False) for v in VARIANTS] + [(v, True) for v in STASH_CHUNK],
+                         ids=lambda c: c[0] + ("-stash" if c[1] else ""))
+def test_wide_forward_chunked_sampled(case):
+    """Wide layer 8192 -> 32768 at n_dyad 16 with 16640 tokens, in more than one token chunk: rows
+    on both sides of every boundary, of the outputs and of the pre-activations kept."""
+    variant, stash = case
+    n_in, n_out, D, M = WIDE
+    banner("permuted_wide", variant, stash)
     X = _draw("X", (M, n_in), 1.0)
     W1 = _draw("W1", (D, n_out // D, n_in // D), 0.02)
     W2 = _draw("W2", (D, n_out // D, n_in // D), 0.02)
     b = _draw("bias", (n_out,), 0.02)
-    y = dy.forward(gpu(X), gpu(W1), gpu(W2), gpu(b), variant=variant)
+    args = (gpu(X), gpu(W1), gpu(W2), gpu(b))
+    if stash:
+        y, h = dy.forward(*args, variant=variant, act="gelu", stash_h=True)
+    else:
+        y, h = dy.forward(*args, variant=variant), None
     torch.cuda.synchronize()
     rng = np.random.default_rng(3)
-    rows = set(rng.choice(M, size=12, replace=False).tolist())
-    rows |= {0, 14335, 14336, 16383, 16384, M - 1}
+    rows = set(rng.choice(M, size=12, replace=False).tolist()) | {0, M - 1}
+    chunk = (STASH_CHUNK if stash else PLAIN_CHUNK)[variant]
+    for m in range(chunk, M, chunk):
+        rows |= {m - 1, m}
     rows = np.array(sorted(rows))
     f64 = lambda t: t.to(torch.float64).numpy()  # noqa: E731
-    ry = oracle.forward(variant, n_in, n_out, D, f64(X[rows]), f64(W1), f64(W2), f64(b))
+    ry, rh = oracle.forward(variant, n_in, n_out, D, f64(X[rows]), f64(W1), f64(W2), f64(b),
+                            act=oracle.ACT_GELU if stash else oracle.ACT_NONE, want_h=True)
     assert_close(y[rows], ry, "bf16", "Y rows")
+    if stash:
+        assert_close(h[rows], rh, "bf16", "H rows")
 
 
 DW_SHAPES = [  # (n_in, n_out, n_dyad, tokens)
