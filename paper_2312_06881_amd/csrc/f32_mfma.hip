@@ -20,8 +20,8 @@
 // (16 bytes at a time, transposed on the way into LDS).
 //
 // Measured on gfx950 against the vector kernels (which keep the other shapes),
-// 768 -> 3072, n_dyad 4, 4096 tokens, Dyad-IT: forward 258 -> 129 us (75
-// TFLOP/s), input gradient 398 -> 127, weight gradient 201 -> 133.
+// 768 -> 3072, n_dyad 4, 4096 tokens, Dyad-IT: forward 259 -> 128 us (75
+// TFLOP/s), input gradient 441 -> 137, weight gradient 212 -> 140.
 #include <type_traits>
 
 #include "dyad_device.h"
@@ -189,7 +189,7 @@ __device__ __forceinline__ void f32_loop(const FSide &sa, const FSide &sb, int64
 }
 
 template <int BM, int BN, bool IN_T, bool OUT_T, bool W_T>
-__global__ void __launch_bounds__(kFThreads, 2) f32_gemm_kernel(GemmPass p, int col_tiles, int row_tiles) {
+__global__ void __launch_bounds__(kFThreads, 2) f32_gemm_kernel(GemmPass p, int col_tiles) {
     constexpr int SM = BM / 32, SN = BN / 32;      // 2 x 2 waves
     __shared__ __attribute__((aligned(16))) float lds[2 * (BM + BN) * kFK];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(kFThreads, 2) f32_gemm_kernel(GemmPass p, int 
 #pragma unroll
         for (int j = 0; j < SN; ++j) {
             const int tb = wn0 + 16 * j;
-            float x[4], h[4];
+            float x[4];
             bool ok[4];
             int64_t e[4];
 #pragma unroll
@@ -273,7 +273,6 @@ __global__ void __launch_bounds__(kFThreads, 2) f32_gemm_kernel(GemmPass p, int 
                 *reinterpret_cast<float4 *>(out + e[0]) = make_float4(x[0], x[1], x[2], x[3]);
                 continue;
             }
-            (void)h;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 if (!ok[v]) continue;
@@ -372,8 +371,8 @@ hipError_t launch_f32_gemm(const GemmPass &p, hipStream_t s) {
     if (blocks >= ((int64_t)1 << 31)) return hipErrorNotSupported;
     auto go = [&](auto in_t, auto out_t, auto w_t) {
         constexpr bool I = decltype(in_t)::value, O = decltype(out_t)::value, W = decltype(w_t)::value;
-        if (wide) f32_gemm_kernel<128, 128, I, O, W><<<(unsigned)blocks, kFThreads, 0, s>>>(p, (int)col_tiles, (int)rt);
-        else f32_gemm_kernel<128, 64, I, O, W><<<(unsigned)blocks, kFThreads, 0, s>>>(p, (int)col_tiles, (int)rt);
+        if (wide) f32_gemm_kernel<128, 128, I, O, W><<<(unsigned)blocks, kFThreads, 0, s>>>(p, (int)col_tiles);
+        else f32_gemm_kernel<128, 64, I, O, W><<<(unsigned)blocks, kFThreads, 0, s>>>(p, (int)col_tiles);
         return hipGetLastError();
     };
     auto with = [&](auto w) {

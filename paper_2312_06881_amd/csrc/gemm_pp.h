@@ -374,14 +374,14 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
         }
     };
     const int wm0 = (wave / WGN) * C::WM, wn0 = (wave % WGN) * C::WN;
-    uint32_t fa[1], fb[W_T ? C::kSubN : 1];
+    uint32_t fb[W_T ? C::kSubN : 1];
     const uint32_t base = (uint32_t)(uintptr_t)lds;
-    fa[0] = base + pp_frag<BM, false>(wm0, 0, lane);
+    const uint32_t fa = base + pp_frag<BM, false>(wm0, 0, lane);
 #pragma unroll
     for (int j = 0; j < (W_T ? C::kSubN : 1); ++j)
         fb[j] = base + (uint32_t)C::kOffB + pp_frag<BN, W_T>(wn0, j, lane);
-    auto addr = [&](int d, int h, uint32_t (&pa)[1], uint32_t (&pb)[W_T ? C::kSubN : 1]) {
-        pa[0] = pp_step<BM, false>(fa[0] + (uint32_t)(d % C::kSlotA * SA::kBytes), h);
+    auto addr = [&](int d, int h, uint32_t &pa, uint32_t (&pb)[W_T ? C::kSubN : 1]) {
+        pa = pp_step<BM, false>(fa + (uint32_t)(d % C::kSlotA * SA::kBytes), h);
 #pragma unroll
         for (int j = 0; j < (W_T ? C::kSubN : 1); ++j)
             pb[j] = pp_step<BN, W_T>(fb[j] + (uint32_t)(d % C::kSlotB * SB::kBytes), h);
@@ -392,8 +392,8 @@ __global__ void __launch_bounds__(kPPThreads, 1) dyad_gemm_pp(GemmArgs a) {
     for (int i = 0; i < C::kSubM; ++i)
 #pragma unroll
         for (int j = 0; j < C::kSubN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    pp_loop<C::kSubM, C::kSubN, false, W_T, 0, 4 * SB::kPitch, SA::kPer, SB::kPer, C::kSlotA, C::kSlotB>(
-        units, wave, acc, issue_a, issue_b, addr, both, [](auto &, auto &) {});
+    pp_loop<C::kSubM, C::kSubN, W_T, 4 * SB::kPitch, SA::kPer, SB::kPer, C::kSlotA, C::kSlotB>(
+        units, wave, acc, issue_a, issue_b, addr, both);
     const int no = kRes ? r * (int)(a.Nout / a.D) + g * (bn / D) + t0 : n0;
     pp_epilogue<C, BM, BN, FORM == kPPSlice, FORM == kPPAdd || FORM == kPPPadAdd,
                 FORM == kPPPadAdd || FORM == kPPPadPair, kRes>(a, smem, acc, m0, no, g, jb, rows_left, lane, wave, wm0,

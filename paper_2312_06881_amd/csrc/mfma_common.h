@@ -109,7 +109,7 @@ __device__ __forceinline__ uint4 deinterleave_uniform(const uint4 (&v)[D], int r
 // move whole 64-byte sectors per four lanes; a lane that loads D consecutive
 // pieces itself leaves its neighbour 16 D bytes away and every 16-byte piece
 // becomes a request of its own (measured on gfx950, all CUs reading from
-// their L2: 9.6 against 26 TB/s).
+// their L2, four pieces a lane: 19 against 38 TB/s).
 // word(w) is applied to each pair of values (an activation, or nothing).
 template <int D, class Word>
 __device__ __forceinline__ void put_residue(const uint4 &v, int r, uint16_t *dst, Word word) {

@@ -6,14 +6,13 @@
 // operand pair.  A side whose reduction index is contiguous in memory (rows of
 // input or untransposed weights) is staged as N rows of 128 bytes, their eight
 // 16-byte chunks XORed by (row >> 1) & 7; a side whose reduction index is the
-// row (transposed weights, both operands of a weight gradient) is staged in
-// its natural layout, 64 rows of N columns, 32-byte chunks swizzled by tr_swz,
-// and read with ds_read_b64_tr_b16.  A global-to-LDS load writes 64 x 16
-// consecutive bytes, so both swizzles are applied to the lane's source
-// address.  Rows of 128 bytes are whole cache lines: with 64-byte rows (32
-// indices) half of every line fetched from the L2 is evicted before its turn
-// (measured on gfx950, all CUs reading a 2.4 MB panel column by column: 15-18
-// against 26-30 TB/s).  Each side has a ring of two or three slots, so a load
+// row (weights read transposed) is staged in its natural layout, 64 rows of N
+// columns, 32-byte chunks swizzled by tr_swz, and read with ds_read_b64_tr_b16.
+// A global-to-LDS load writes 64 x 16 consecutive bytes, so both swizzles are
+// applied to the lane's source address.  Rows of 128 bytes are whole cache
+// lines: with 64-byte rows (32 indices) half of every line fetched from the L2
+// is evicted before its turn (measured on gfx950, all CUs reading a 2.4 MB panel
+// column by column: 16 against 35 TB/s).  Each side has a ring of two or three slots, so a load
 // has one or two units of matrix work (1 - 2 us) to arrive.
 //
 // Ping-pong.  Waves w and w + 4 share a SIMD.  The two halves of the workgroup
@@ -130,13 +129,10 @@ __device__ __forceinline__ void pp_barrier() {
 // ---- fragment reads: SM fragments of side A and SN of side B ----------------
 #define PP_RA(i, off) "ds_read_b128 %[a" #i "], %[pa] offset:" #off "\n\t"
 #define PP_RB(i, off) "ds_read_b128 %[b" #i "], %[pb] offset:" #off "\n\t"
-#define PP_TA(i) "ds_read_b64_tr_b16 %[al" #i "], %[pa" #i "]\n\tds_read_b64_tr_b16 %[ah" #i "], %[pa" #i "] offset:%[sa]\n\t"
 #define PP_TB(i) "ds_read_b64_tr_b16 %[bl" #i "], %[pb" #i "]\n\tds_read_b64_tr_b16 %[bh" #i "], %[pb" #i "] offset:%[sb]\n\t"
 #define PP_OA(i) [a##i] "=&v"(a[i])
 #define PP_OB(i) [b##i] "=&v"(b[i])
-#define PP_OTA(i) [al##i] "=&v"(al[i]), [ah##i] "=&v"(ah[i])
 #define PP_OTB(i) [bl##i] "=&v"(bl[i]), [bh##i] "=&v"(bh[i])
-#define PP_IA(i) [pa##i] "v"(pa[i])
 #define PP_IB(i) [pb##i] "v"(pb[i])
 #define PP_RA2 PP_RA(0, 0) PP_RA(1, 2048)
 #define PP_RA4 PP_RA(0, 0) PP_RA(1, 2048) PP_RA(2, 4096) PP_RA(3, 6144)
@@ -144,9 +140,6 @@ __device__ __forceinline__ void pp_barrier() {
 #define PP_RB2 PP_RB(0, 0) PP_RB(1, 2048)
 #define PP_RB4 PP_RB2 PP_RB(2, 4096) PP_RB(3, 6144)
 #define PP_RB6 PP_RB4 PP_RB(4, 8192) PP_RB(5, 10240)
-#define PP_TA2 PP_TA(0) PP_TA(1)
-#define PP_TA4 PP_TA(0) PP_TA(1) PP_TA(2) PP_TA(3)
-#define PP_TA8 PP_TA4 PP_TA(4) PP_TA(5) PP_TA(6) PP_TA(7)
 #define PP_TB2 PP_TB(0) PP_TB(1)
 #define PP_TB4 PP_TB2 PP_TB(2) PP_TB(3)
 #define PP_TB6 PP_TB4 PP_TB(4) PP_TB(5)
@@ -156,46 +149,34 @@ __device__ __forceinline__ void pp_barrier() {
 #define PP_OB2 PP_OB(0), PP_OB(1)
 #define PP_OB4 PP_OB2, PP_OB(2), PP_OB(3)
 #define PP_OB6 PP_OB4, PP_OB(4), PP_OB(5)
-#define PP_OTA2 PP_OTA(0), PP_OTA(1)
-#define PP_OTA4 PP_OTA(0), PP_OTA(1), PP_OTA(2), PP_OTA(3)
-#define PP_OTA8 PP_OTA4, PP_OTA(4), PP_OTA(5), PP_OTA(6), PP_OTA(7)
 #define PP_OTB2 PP_OTB(0), PP_OTB(1)
 #define PP_OTB4 PP_OTB2, PP_OTB(2), PP_OTB(3)
 #define PP_OTB6 PP_OTB4, PP_OTB(4), PP_OTB(5)
-#define PP_IA2 PP_IA(0), PP_IA(1)
-#define PP_IA4 PP_IA(0), PP_IA(1), PP_IA(2), PP_IA(3)
-#define PP_IA8 PP_IA4, PP_IA(4), PP_IA(5), PP_IA(6), PP_IA(7)
 #define PP_IB2 PP_IB(0), PP_IB(1)
 #define PP_IB4 PP_IB2, PP_IB(2), PP_IB(3)
 #define PP_IB6 PP_IB4, PP_IB(4), PP_IB(5)
 #define PP_WAIT "s_waitcnt lgkmcnt(0)"
 // B first, then A: the multiplies walk A within one B
 #define PP_READ_RR(NA, NB)                                                                                     \
-    asm volatile(PP_RB##NB PP_RA##NA PP_WAIT : PP_OA##NA, PP_OB##NB : [pa] "v"(pa[0]), [pb] "v"(pb[0]) : "memory")
+    asm volatile(PP_RB##NB PP_RA##NA PP_WAIT : PP_OA##NA, PP_OB##NB : [pa] "v"(pa), [pb] "v"(pb[0]) : "memory")
 #define PP_READ_RT(NA, NB)                                                                                     \
     asm volatile(PP_TB##NB PP_RA##NA PP_WAIT                                                                   \
                  : PP_OA##NA, PP_OTB##NB                                                                       \
-                 : [pa] "v"(pa[0]), PP_IB##NB, [sb] "n"(SB)                                                    \
-                 : "memory")
-#define PP_READ_TT(NA, NB)                                                                                     \
-    asm volatile(PP_TB##NB PP_TA##NA PP_WAIT                                                                   \
-                 : PP_OTA##NA, PP_OTB##NB                                                                      \
-                 : PP_IA##NA, PP_IB##NB, [sa] "n"(SA), [sb] "n"(SB)                                            \
+                 : [pa] "v"(pa), PP_IB##NB, [sb] "n"(SB)                                                       \
                  : "memory")
 #define PP_CASE(NA, NB)                                                                                        \
     if constexpr (SM == NA && SN == NB) {                                                                      \
-        if constexpr (!TA && !TB) PP_READ_RR(NA, NB);                                                          \
-        else if constexpr (!TA && TB) PP_READ_RT(NA, NB);                                                      \
-        else PP_READ_TT(NA, NB);                                                                               \
+        if constexpr (!TB) PP_READ_RR(NA, NB);                                                                 \
+        else PP_READ_RT(NA, NB);                                                                               \
     }
 
-// pa / pb: LDS addresses of the fragments (without TR only the first is used);
-// SA / SB: bytes from a TR fragment's first four rows to its next four.
-template <int SM, int SN, bool TA, bool TB, int SA, int SB>
-__device__ __forceinline__ void pp_read(const uint32_t (&pa)[TA ? SM : 1], const uint32_t (&pb)[TB ? SN : 1],
-                                        bf16x8_t (&a)[SM], bf16x8_t (&b)[SN]) {
-    static_assert(TB || !TA, "a transposed A side comes with a transposed B side");
-    bf16x4_t al[SM], ah[SM], bl[SN], bh[SN];
+// pa / pb: LDS addresses of the fragments (side A's and, without TB, side B's
+// are 16 rows apart from the first); SB: bytes from a transposed fragment's
+// first four rows to its next four.
+template <int SM, int SN, bool TB, int SB>
+__device__ __forceinline__ void pp_read(uint32_t pa, const uint32_t (&pb)[TB ? SN : 1], bf16x8_t (&a)[SM],
+                                        bf16x8_t (&b)[SN]) {
+    bf16x4_t bl[SN], bh[SN];
     PP_CASE(8, 4)
     PP_CASE(4, 6)
     PP_CASE(4, 4)
@@ -203,10 +184,6 @@ __device__ __forceinline__ void pp_read(const uint32_t (&pa)[TA ? SM : 1], const
     PP_CASE(2, 2)
     static_assert((SM == 8 && SN == 4) || (SM == 4 && (SN == 6 || SN == 4 || SN == 2)) || (SM == 2 && SN == 2),
                   "a fragment read exists");
-    if constexpr (TA) {
-#pragma unroll
-        for (int i = 0; i < SM; ++i) a[i] = __builtin_shufflevector(al[i], ah[i], 0, 1, 2, 3, 4, 5, 6, 7);
-    }
     if constexpr (TB) {
 #pragma unroll
         for (int j = 0; j < SN; ++j) b[j] = __builtin_shufflevector(bl[j], bh[j], 0, 1, 2, 3, 4, 5, 6, 7);
@@ -218,16 +195,15 @@ __device__ __forceinline__ void pp_read(const uint32_t (&pa)[TA ? SM : 1], const
 // d % SLOTB (for d >= units they load a valid unit again: its slot is never
 // read); addr(d, h, pa, pb) gives the fragment addresses of step h;
 // both(d) says whether unit d has two steps to multiply, or the second alone.
-// LDS is free, and no load is
-// in flight, when it returns (after a barrier).
+// LDS is free, and no load is in flight, when it returns (after a barrier).
 // Side B's fragments are the first MFMA operand, so a lane's four sums lie
 // along side B (4 (l / 16) + v) at row l % 16 of side A.
-template <int SM, int SN, bool TA, bool TB, int SA, int SB, int NVA, int NVB, int SLOTA, int SLOTB, class IssueA,
-          class IssueB, class Addr, class Both, class Extra>
+template <int SM, int SN, bool TB, int SB, int NVA, int NVB, int SLOTA, int SLOTB, class IssueA, class IssueB,
+          class Addr, class Both>
 __device__ __forceinline__ void pp_loop(int units, int wave, f32x4_t (&acc)[SM][SN], IssueA issue_a, IssueB issue_b,
-                                        Addr addr, Both both, Extra extra) {
+                                        Addr addr, Both both) {
     bf16x8_t a[SM], b[SN];
-    uint32_t pa[TA ? SM : 1], pb[TB ? SN : 1];
+    uint32_t pa, pb[TB ? SN : 1];
     const bool half = wave >= kPPWaves / 2;
     // loads still allowed in flight when unit d + 1 must have arrived, after
     // unit d's issues (B of unit d + SLOTB - 1, then A of unit d + SLOTA - 1)
@@ -247,19 +223,18 @@ __device__ __forceinline__ void pp_loop(int units, int wave, f32x4_t (&acc)[SM][
 #pragma unroll
             for (int i = 0; i < SM; ++i)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-        extra(a, b);
         __builtin_amdgcn_s_setprio(0);
     };
     for (int d = 0; d < units; ++d) {
         issue_b(d + SLOTB - 1);
         addr(d, 0, pa, pb);
-        pp_read<SM, SN, TA, TB, SA, SB>(pa, pb, a, b);
+        pp_read<SM, SN, TB, SB>(pa, pb, a, b);
         pp_barrier();
         if (both(d)) multiply();
         pp_barrier();
         issue_a(d + SLOTA - 1);
         addr(d, 1, pa, pb);
-        pp_read<SM, SN, TA, TB, SA, SB>(pa, pb, a, b);
+        pp_read<SM, SN, TB, SB>(pa, pb, a, b);
         if (half) wait_vm<kLeft>();
         pp_barrier();
         multiply();
