@@ -18,8 +18,8 @@
  * (appendix, caveat on rectangular W): the layer acts as the one of widths
  * D*bi -> D*bo on X with zero columns appended, and only its first n_out
  * outputs exist.  Entries whose row is >= n_out or whose column is >= n_in
- * have no effect, and their gradients are zero.  Such widths run on the
- * general kernels.
+ * have no effect, and their gradients are zero.  Such widths run on
+ * zero-padded copies of the blocks or on the general kernels.
  *
  * Layouts: every activation is token-major and row-major: X[M][n_in],
  * Y, H, dZ [M][n_out], dX, H_in [M][n_in]; W1, W2, dW1, dW2 as above; bias and
@@ -39,16 +39,22 @@
  * per-device memory pool the first time that stream needs it, regrown in
  * stream order when a later call needs more, and kept until the process
  * ends.  It holds the fp32 partial sums of a split reduction (small batches,
- * few output tiles; a few slices of M x n_out fp32, at most 2 GiB) and, at
- * n_dyad 3, 6, 8 and 16 with large batches, a de-interleaved copy of the
- * input and fp32 slices of the output; for shapes the fused tiles refuse
- * (from 512 tokens), zero-padded block copies of the input and the weights
- * and one fp32 slice (each form within 2 GiB; the tokens are taken in chunks
- * beyond that).  Calls on one stream share it in stream order; calls on
- * different streams never share it.  While the stream is being captured into
- * a graph the buffer is never allocated or regrown; when it cannot be had
- * (capture, or the pool fails), the call runs a plan that needs none, with
- * the same results.
+ * few output tiles; a few slices of M x n_out fp32, at most 2 GiB); with large
+ * batches at n_dyad 2, 3, 4, 6, 8 and 16, by the token chunk, a de-interleaved
+ * copy of the input, fp32 slices of the output or its bf16 results before
+ * they are interleaved, and for an input gradient a copy of W1; for shapes
+ * the fused tiles refuse (from 512 tokens), zero-padded block copies of the
+ * input and the weights and one fp32 slice (each form within 2 GiB; the
+ * tokens are taken in chunks beyond that).  Calls on one stream share it in
+ * stream order, from several host threads too: a call holds the buffer until
+ * its last launch is enqueued.  Calls on different streams never share it.
+ * While the stream is being captured into a graph the buffer is never
+ * allocated or regrown; when it cannot be had (capture, or the pool fails),
+ * the call runs a plan that needs none, with the same results up to the order
+ * of the fp32 sums.  A call captured while its stream has a buffer uses that buffer at every replay (it
+ * is kept for the graph if the stream's is regrown later), so replays and
+ * other calls on the stream the graph was captured from must be ordered with
+ * each other; where they are not, capture on a stream that no other call uses.
  * Every call only enqueues work on `stream`
  * (NULL = the null stream) and returns without synchronising; results are
  * valid once that work completes.  Outputs are overwritten, never accumulated

@@ -163,10 +163,11 @@ class DyadLinear(torch.nn.Module):
     """Dyad replacement for ``torch.nn.Linear(in_features, out_features)``.
 
     A width that ``n_dyad`` does not divide is zero-padded up to the next multiple
-    (appendix, caveat on rectangular W); such layers run on the library's general
-    kernels rather than the matrix-core ones.  Initialisation (a convenience, not
-    part of the method): uniform in +-1/sqrt(2 * in_features / n_dyad), the
-    fan-in of one output feature (two components of in_features / n_dyad inputs each).
+    (appendix, caveat on rectangular W); such layers run on zero-padded copies of
+    their blocks from 512 tokens, and on the general kernels below.  Initialisation
+    (a convenience, not part of the method): uniform in +-1/sqrt(2 * in_features /
+    n_dyad), the fan-in of one output feature (two components of in_features /
+    n_dyad inputs each).
     """
 
     def __init__(self, in_features, out_features, n_dyad, variant="IT", bias=True, device=None,

@@ -1,5 +1,6 @@
-"""Inference without autograd: the same results as the recorded path, which every call that could
-need a derivative still takes."""
+"""Inference without autograd: the same results as the recorded path (up to the order of fp32 sums
+where a stashed pre-activation changes the form), which every call that could need a derivative
+still takes."""
 import pytest
 import torch
 from torch.autograd import forward_ad
