@@ -47,7 +47,9 @@
  * input and the weights and one fp32 slice (each form within 2 GiB; the
  * tokens are taken in chunks beyond that).  Calls on one stream share it in
  * stream order, from several host threads too: a call holds the buffer until
- * its last launch is enqueued.  Calls on different streams never share it.
+ * its last launch is enqueued.  Calls on different streams never share it,
+ * but for hipStreamPerThread: its buffer is one for all threads, and a call of
+ * another thread than the last waits on the GPU for that one's work.
  * While the stream is being captured into a graph the buffer is never
  * allocated or regrown; when it cannot be had (capture, or the pool fails),
  * the call runs a plan that needs none, with the same results up to the order

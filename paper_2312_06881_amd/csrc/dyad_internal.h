@@ -111,23 +111,38 @@ class WorkspaceHold {
 public:
     WorkspaceHold() : prev_(t_current) { t_current = this; }
     ~WorkspaceHold() {
-        if (mu_) mu_->unlock();
+        release();
         t_current = prev_;
     }
     WorkspaceHold(const WorkspaceHold &) = delete;
     WorkspaceHold &operator=(const WorkspaceHold &) = delete;
     static WorkspaceHold *current() { return t_current; }
-    void take(std::mutex &mu) {
-        if (mu_ == &mu) return;   // a pass that asks again
-        if (mu_) mu_->unlock();
+    // True if the pass did not hold `mu` yet.
+    bool take(std::mutex &mu) {
+        if (mu_ == &mu) return false;   // a pass that asks again
+        release();
         mu_ = &mu;
         mu.lock();
+        return true;
+    }
+    // At the end of the pass, before the lock is given back.
+    void at_end(void (*f)(hipEvent_t), hipEvent_t e) {
+        end_ = f;
+        event_ = e;
     }
 
 private:
+    void release() {
+        if (end_) end_(event_);
+        end_ = nullptr;
+        if (mu_) mu_->unlock();
+        mu_ = nullptr;
+    }
     static inline thread_local WorkspaceHold *t_current = nullptr;
     WorkspaceHold *prev_;
     std::mutex *mu_ = nullptr;
+    void (*end_)(hipEvent_t) = nullptr;
+    hipEvent_t event_ = nullptr;
 };
 
 // dyad_forward_noalloc: while a ScratchScope lives on the calling thread,

@@ -10,9 +10,15 @@
 // last launch is enqueued (WorkspaceHold): a few tens of nanoseconds when nobody
 // else calls on that stream.
 //
+// hipStreamPerThread is one handle for a stream of each thread.  Its buffer is
+// one all the same (threads come and go, so one for each would have no bound):
+// a pass leaves an event behind, and a pass of another thread makes its own
+// stream wait for it.
+//
 // Graphs.  A buffer handed out while its stream is being captured is part of
 // the captured graph: it is never freed, so a replay after the stream's buffer
 // was regrown still writes to memory of its own.
+#include <atomic>
 #include <new>
 
 #include "dyad_internal.h"
@@ -27,6 +33,8 @@ struct StreamBuffer {
     void *ptr = nullptr;
     size_t bytes = 0;
     bool in_graph = false;   // a captured graph refers to ptr
+    uint64_t thread = 0;     // hipStreamPerThread: whose pass was the last,
+    hipEvent_t end = nullptr;   // and its end
     StreamBuffer *next;
     StreamBuffer(int d, hipStream_t s, StreamBuffer *n) : dev(d), stream(s), next(n) {}
 };
@@ -67,6 +75,37 @@ hipError_t pool_of(int dev, hipMemPool_t *out) {
     return hipSuccess;
 }
 
+// A number for the calling thread that no later thread gets again.
+uint64_t thread_number() {
+    static std::atomic<uint64_t> count{0};
+    static thread_local const uint64_t mine = ++count;
+    return mine;
+}
+
+void mark_end(hipEvent_t e) {
+    if (hipEventRecord(e, hipStreamPerThread) == hipSuccess) return;
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(hipStreamPerThread);
+}
+
+// Orders the calling thread's own stream behind the last pass on `b`.
+hipError_t order_threads(StreamBuffer *b, WorkspaceHold *hold, bool capturing) {
+    const uint64_t me = thread_number();
+    if (capturing)   // (a captured stream cannot wait for work outside its graph)
+        return b->thread == me ? hipSuccess : hipErrorNotSupported;
+    if (!b->end) {
+        hipError_t e = hipEventCreateWithFlags(&b->end, hipEventDisableTiming);
+        if (e != hipSuccess) return e;
+    }
+    if (b->thread != 0 && b->thread != me) {
+        hipError_t e = hipStreamWaitEvent(hipStreamPerThread, b->end, 0);
+        if (e != hipSuccess) return e;
+    }
+    b->thread = me;
+    hold->at_end(mark_end, b->end);
+    return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t split_workspace(hipStream_t s, size_t bytes, void **out) {
@@ -83,10 +122,14 @@ hipError_t split_workspace(hipStream_t s, size_t bytes, void **out) {
     if (!hold) return hipErrorNotSupported;   // nothing would order this pass's launches
     StreamBuffer *b = buffer_of(dev, s);
     if (!b) return hipErrorOutOfMemory;
-    hold->take(b->mu);
+    const bool first = hold->take(b->mu);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     e = hipStreamIsCapturing(s, &cap);
     const bool capturing = e == hipSuccess && cap != hipStreamCaptureStatusNone;
+    if (s == hipStreamPerThread && first) {
+        const hipError_t o = order_threads(b, hold, capturing);
+        if (o != hipSuccess) return o;
+    }
     if (b->bytes >= bytes) {
         if (e != hipSuccess) (void)hipGetLastError();
         b->in_graph = b->in_graph || capturing;

@@ -1,6 +1,7 @@
 // Host-only check of the per-stream scratch buffer (stream_workspace.hip) with a
 // mock of the HIP calls it makes, built under ThreadSanitizer: two host threads
-// on one stream, two streams, and a buffer that a captured graph refers to.
+// on one stream, two streams, the stream handle that is another stream in each
+// thread, and a buffer that a captured graph refers to.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -14,6 +15,9 @@ namespace {
 std::mutex g_mock;
 bool g_capturing = false;
 std::vector<void *> g_freed;
+// events, as the work of a thread's own stream that they stand for
+std::vector<std::thread::id> g_recorded;
+std::vector<std::pair<std::thread::id, std::thread::id>> g_waits;   // (who waits, for whom)
 
 }  // namespace
 
@@ -37,6 +41,25 @@ hipError_t hipFreeAsync(void *p, hipStream_t) {
     g_freed.push_back(p);      // kept allocated: its address stays its own
     return hipSuccess;
 }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    std::lock_guard<std::mutex> lock(g_mock);
+    g_recorded.emplace_back();
+    *e = (hipEvent_t)g_recorded.size();
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(g_mock);
+    if (s != hipStreamPerThread) return hipErrorInvalidHandle;
+    g_recorded[(size_t)e - 1] = std::this_thread::get_id();
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    std::lock_guard<std::mutex> lock(g_mock);
+    if (s != hipStreamPerThread) return hipErrorInvalidHandle;
+    g_waits.emplace_back(std::this_thread::get_id(), g_recorded[(size_t)e - 1]);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 
 }  // extern "C"
 
@@ -99,6 +122,31 @@ int main() {
         EXPECT(a && b && a != b);
         // asked again within the pass: the same buffer
         EXPECT(split_workspace(s1, 2048, &p) == hipSuccess && p == a);
+    }
+
+    // one handle, a stream of each thread: a pass waits for the last one of another thread
+    {
+        std::vector<std::pair<std::thread::id, std::thread::id>> expect;
+        const std::thread::id me = std::this_thread::get_id();
+        EXPECT(pass(hipStreamPerThread, 1, 4096) == 0);
+        EXPECT(pass(hipStreamPerThread, 2, 4096) == 0);
+        EXPECT(g_waits.empty());
+        std::thread other([&] {
+            EXPECT(pass(hipStreamPerThread, 3, 4096) == 0);
+            EXPECT(pass(hipStreamPerThread, 4, (size_t)2 << 20) == 0);
+            expect.emplace_back(std::this_thread::get_id(), me);
+            expect.emplace_back(me, std::this_thread::get_id());
+        });
+        other.join();
+        EXPECT(pass(hipStreamPerThread, 5, 4096) == 0);
+        EXPECT(g_waits == expect);
+        // under capture a wait for another thread's work has no place: no buffer
+        g_capturing = true;
+        EXPECT(pass(hipStreamPerThread, 6, 4096) == 0);
+        std::thread late([&] { EXPECT(pass(hipStreamPerThread, 7, 4096) != 0); });
+        late.join();
+        g_capturing = false;
+        EXPECT(g_waits == expect);
     }
 
     // under capture: the buffer that is there, never a new one; and it outlives a later growth

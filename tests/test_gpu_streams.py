@@ -1,5 +1,5 @@
 """The library's per-stream scratch buffer on the GPU: two host threads calling on
-one stream, and a captured graph whose stream's buffer grows afterwards.  Every
+one stream and on the stream handle that is each thread's own, and a captured graph whose stream's buffer grows afterwards.  Every
 result is compared bit for bit with the same call made alone."""
 import threading
 
@@ -48,6 +48,34 @@ def test_two_threads_on_one_stream(case):
         t.join()
     torch.cuda.synchronize()
     assert [int(w) for w in wrong] == [0, 0]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_each_threads_own_stream(case):
+    n_in, n_out, D, M = case
+    print("CASE own streams", *case, flush=True)
+    inputs = [layer(case, s) for s in (4, 5)]
+    alone = [dy.forward(*i, variant="IT") for i in inputs]
+    out = [torch.zeros((20, M, n_out), dtype=torch.bfloat16, device=DEV) for _ in inputs]
+    torch.cuda.synchronize()
+    codes = [[], []]
+
+    def work(n):
+        x, w1, w2 = inputs[n]
+        for y in out[n]:
+            codes[n].append(dy.dyad_forward(dy.IT, n_in, n_out, D, M, dy.BF16, x.data_ptr(), w1.data_ptr(),
+                                            w2.data_ptr(), None, dy.ACT_NONE, y.data_ptr(), None,
+                                            2))   # hipStreamPerThread
+        torch.cuda.synchronize()
+
+    threads = [threading.Thread(target=work, args=(n,)) for n in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert codes == [[0] * 20] * 2
+    for y, a in zip(out, alone):
+        assert torch.equal(y, a.expand_as(y))
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
